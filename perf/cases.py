@@ -11,8 +11,8 @@ A case is a dict of plain values; `kind` names the call sequence:
   mlp      nb_mlp_grad: loss and gradient of one training minibatch of the buffer predictor
 
 The particles are rigid SPC/E waters at liquid density.  To be quick to make at every size they sit on a jittered
-lattice with random vacancies and random orientations (O-O distances from about 0.25 nm), and move ballistically
-at 300 K with 2 fs steps between list builds.  Units: nm, ps, kJ/mol, e, u.
+lattice, bent by smooth shears, with random vacancies and orientations (O-O distances from about 0.2 nm), and move
+ballistically at 300 K with 2 fs steps between list builds.  Units: nm, ps, kJ/mol, e, u.
 """
 import math
 
@@ -103,7 +103,7 @@ def draw(rng):
     if kind == "prune":
         rc = min(rc, round(half - 0.31, 3))
         return _md(None, kind, waters, shape, rc, rc + 0.3, aspect=aspect, nstlist=rng.randint(3, 6))
-    virial = rng.random() < 0.25
+    virial = waters >= 20000 and rng.random() < 0.5   # pressure-coupled steps: boxes of production size
     energy = virial or rng.random() < 0.6
     return _md(None, kind, waters, shape, rc, round(rc + rng.uniform(0.05, 0.15), 3), aspect=aspect,
                nstlist=rng.randint(5, 20) if kind == "cycle" else 10, energy=energy, virial=virial,
@@ -126,6 +126,10 @@ def _water(rng, waters, box):
     pick = rng.permutation(int(sites.prod()))[:waters]
     cell = np.stack(np.unravel_index(pick, sites), axis=1)
     o = (cell + 0.5 + rng.uniform(-0.1, 0.1, (waters, 3))) * (box / sites)
+    # gentle periodic shears (each keeps the density) bend the lattice rows, so that no grid is aligned with them
+    for d, (p, q) in enumerate(((1, 2), (2, 0), (0, 1))):
+        waves = np.sin(2.0 * np.pi * (o[:, (p, q)] / box[[p, q]] + rng.uniform(0.0, 1.0, 2))).sum(1)
+        o[:, d] += 0.45 * box[d] / sites[d] * waves
     u = rng.standard_normal((waters, 3))
     u /= np.linalg.norm(u, axis=1, keepdims=True)
     w = rng.standard_normal((waters, 3))
