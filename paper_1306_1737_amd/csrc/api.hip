@@ -1179,6 +1179,7 @@ void nb_mlp_free(nb_mlp *m) {
     if (m->ctx->mlp == m) m->ctx->mlp = nullptr;
     DevBuf *bufs[] = {&m->params, &m->m, &m->v, &m->step, &m->lo, &m->hi};
     for (DevBuf *b : bufs) release(*b);
+    for (nb_mlp::Scratch &e : m->scratch) release(e.buf);
     delete m;
 }
 

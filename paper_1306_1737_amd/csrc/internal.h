@@ -7,6 +7,7 @@
 #include <atomic>
 #include <cstdint>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <utility>
 #include <vector>
@@ -195,6 +196,13 @@ struct nb_mlp {
     double dom_target = 0, dom_dt = 0, dom_brc = 0;
     int dom_ntypes = 0;
     std::vector<double> dom_charge, dom_c6c12;
+    // gradient rows of a spread minibatch, one buffer per stream that trained the model
+    struct Scratch {
+        hipStream_t stream = nullptr;
+        mxn::DevBuf buf;
+    };
+    Scratch scratch[4];
+    std::mutex mu;   // a training call's two launches stay together
 };
 
 namespace mxn {

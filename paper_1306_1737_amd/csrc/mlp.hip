@@ -14,6 +14,13 @@
 // accumulators) in registers.  Hidden activations and the layer-2 deltas are
 // broadcast through LDS; the column access W2^T delta2 reads a padded LDS
 // copy of W2 without bank conflicts.
+//
+// A sample is a chain of about 2 us on one wavefront (LDS round trips, tanh,
+// the output sum), so a minibatch on one workgroup is bound by that chain
+// times batch / 4.  The batch is therefore spread over up to kMlpParts
+// workgroups, each writing the gradient of its share to scratch; a second
+// launch sums the shares in a fixed order and applies Adam (256 samples: 144
+// us a call on one workgroup, 13.3 us on 64).
 #include "internal.h"
 
 namespace {
@@ -22,6 +29,9 @@ constexpr int NF = 8, NH = 64;
 constexpr int OFF_W1 = 0, OFF_B1 = NH * NF, OFF_W2 = OFF_B1 + NH, OFF_B2 = OFF_W2 + NH * NH, OFF_W3 = OFF_B2 + NH,
               OFF_B3 = OFF_W3 + NH, NPARAM = OFF_B3 + 1;
 static_assert(NPARAM == 4801, "parameter count");
+constexpr int kMlpParts = 128;                          // most workgroups a batch is spread over
+constexpr int kMlpRow = (NPARAM + 1 + 63) / 64 * 64;    // floats per gradient row: parameters, then the loss sum
+
 
 struct MlpArgs {
     float *params, *m, *v;
@@ -32,6 +42,7 @@ struct MlpArgs {
     float lr;
     float *loss;
     float *grad_out;   // non-null: write the batch gradient, do not update
+    float *parts;      // gradient rows of the workgroups (kMlpRow floats each)
     float *y_out;      // inference output
 };
 
@@ -51,13 +62,31 @@ __device__ inline float softplus(float z) { return fmaxf(z, 0.0f) + log1pf(expf(
 
 __device__ inline float sigmoid(float z) { return 1.0f / (1.0f + expf(-z)); }
 
+constexpr int GROW = NH + 1;   // padded W2 gradient rows in LDS: lane j's element i lies in bank (j + i) mod 32
+// LDS address of flat parameter p (the W2 block padded), and of the loss sum after the last parameter
+__device__ inline int gaddr(int p) {
+    return p < OFF_W2 ? p : (p < OFF_B2 ? OFF_W2 + (p - OFF_W2) / NH * GROW + (p - OFF_W2) % NH : p + NH);
+}
+
+__device__ inline void adam(const MlpArgs &a, int i, float g, int t) {
+    const float c1 = 1.0f / (1.0f - powf(0.9f, (float)t)), c2 = 1.0f / (1.0f - powf(0.999f, (float)t));
+    const float m = 0.9f * a.m[i] + 0.1f * g;
+    const float v = 0.999f * a.v[i] + 0.001f * g * g;
+    a.m[i] = m;
+    a.v[i] = v;
+    a.params[i] -= a.lr * (m * c1) / (sqrtf(v * c2) + 1e-8f);
+}
+
+// Gradient of the samples s = wave, wave + waves, ... of this workgroup.
+// PARTS: the sums go to this workgroup's row of a.parts (k_mlp_finish adds
+// the rows); otherwise one workgroup holds the whole batch and finishes it.
+template <bool PARTS>
 __global__ __launch_bounds__(256) void k_mlp_step(MlpArgs a) {
     __shared__ float w2s[NH * (NH + 1)];
     __shared__ float h1s[4][NH], d2s[4][NH];
-    __shared__ float gacc[NPARAM + 1];   // gradient, then the loss sum
+    __shared__ float gacc[NPARAM + 1 + NH];   // gradient (gaddr order), then the loss sum
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     for (int i = tid; i < NH * NH; i += 256) w2s[(i / NH) * (NH + 1) + i % NH] = a.params[OFF_W2 + i];
-    for (int i = tid; i <= NPARAM; i += 256) gacc[i] = 0.0f;
     __syncthreads();
     float w1[NF], gw1[NF], w2[NH], gw2[NH], lo[NF], sc[NF];
 #pragma unroll
@@ -76,7 +105,7 @@ __global__ __launch_bounds__(256) void k_mlp_step(MlpArgs a) {
     const float b3 = a.params[OFF_B3];
     float gb1 = 0.0f, gb2 = 0.0f, gw3 = 0.0f, gb3 = 0.0f, lsum = 0.0f;
     const float inv_b = 2.0f / (float)a.batch;
-    for (int s = w; s < a.batch; s += 4) {
+    for (int s = blockIdx.x * 4 + w; s < a.batch; s += gridDim.x * 4) {
         float x[NF];
 #pragma unroll
         for (int i = 0; i < NF; ++i) x[i] = (a.X[s * NF + i] - lo[i]) * sc[i] - 1.0f;
@@ -111,35 +140,61 @@ __global__ __launch_bounds__(256) void k_mlp_step(MlpArgs a) {
         for (int i = 0; i < NF; ++i) gw1[i] = fmaf(d1, x[i], gw1[i]);
         wave_sync_lds();   // before the next sample overwrites h1s / d2s
     }
+    // the four wavefronts' sums, added in wavefront order
+    for (int k = 0; k < 4; ++k) {
+        if (w == k) {
+            auto put = [&](int at, float v) { gacc[at] = k == 0 ? v : gacc[at] + v; };
 #pragma unroll
-    for (int i = 0; i < NF; ++i) atomicAdd(&gacc[OFF_W1 + lane * NF + i], gw1[i]);
-    atomicAdd(&gacc[OFF_B1 + lane], gb1);
+            for (int i = 0; i < NF; ++i) put(OFF_W1 + lane * NF + i, gw1[i]);
+            put(OFF_B1 + lane, gb1);
 #pragma unroll
-    for (int i = 0; i < NH; ++i) atomicAdd(&gacc[OFF_W2 + lane * NH + i], gw2[i]);
-    atomicAdd(&gacc[OFF_B2 + lane], gb2);
-    atomicAdd(&gacc[OFF_W3 + lane], gw3);
-    if (lane == 0) {
-        atomicAdd(&gacc[OFF_B3], gb3);
-        atomicAdd(&gacc[NPARAM], lsum);
+            for (int i = 0; i < NH; ++i) put(OFF_W2 + lane * GROW + i, gw2[i]);
+            put(gaddr(OFF_B2) + lane, gb2);
+            put(gaddr(OFF_W3) + lane, gw3);
+            if (lane == 0) {
+                put(gaddr(OFF_B3), gb3);
+                put(gaddr(NPARAM), lsum);
+            }
+        }
+        __syncthreads();
     }
+    if constexpr (PARTS) {
+        float *row = a.parts + (size_t)blockIdx.x * kMlpRow;
+        for (int i = tid; i <= NPARAM; i += 256) row[i] = gacc[gaddr(i)];
+        if (!a.grad_out && blockIdx.x == 0 && tid == 0) *a.step += 1;   // read by k_mlp_finish
+    } else {
+        if (a.loss && tid == 0) *a.loss = gacc[gaddr(NPARAM)] / (float)a.batch;
+        const int t = *a.step + 1;
+        for (int i = tid; i < NPARAM; i += 256) {
+            if (a.grad_out) a.grad_out[i] = gacc[gaddr(i)];
+            else adam(a, i, gacc[gaddr(i)], t);
+        }
+        __syncthreads();
+        if (!a.grad_out && tid == 0) *a.step = t;
+    }
+}
+
+// Sum of the workgroups' gradient rows (64 parameters per workgroup; each of its wavefronts adds every
+// fourth row, the four sums are added in order), then Adam or the gradient output; the loss is value NPARAM.
+__global__ __launch_bounds__(256) void k_mlp_finish(MlpArgs a, int nparts) {
+    __shared__ float red[4][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i = blockIdx.x * 64 + lane;
+    float s = 0.0f;
+    if (i <= NPARAM) {
+#pragma unroll 8
+        for (int k = w; k < nparts; k += 4) s += a.parts[(size_t)k * kMlpRow + i];
+    }
+    red[w][lane] = s;
     __syncthreads();
-    if (a.loss && tid == 0) *a.loss = gacc[NPARAM] / (float)a.batch;
-    if (a.grad_out) {
-        for (int i = tid; i < NPARAM; i += 256) a.grad_out[i] = gacc[i];
-        return;
+    if (w > 0 || i > NPARAM) return;
+    const float g = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+    if (i == NPARAM) {
+        if (a.loss) *a.loss = g / (float)a.batch;
+    } else if (a.grad_out) {
+        a.grad_out[i] = g;
+    } else {
+        adam(a, i, g, *a.step);
     }
-    const int t = *a.step + 1;
-    const float c1 = 1.0f / (1.0f - powf(0.9f, (float)t)), c2 = 1.0f / (1.0f - powf(0.999f, (float)t));
-    for (int i = tid; i < NPARAM; i += 256) {
-        const float g = gacc[i];
-        const float m = 0.9f * a.m[i] + 0.1f * g;
-        const float v = 0.999f * a.v[i] + 0.001f * g * g;
-        a.m[i] = m;
-        a.v[i] = v;
-        a.params[i] -= a.lr * (m * c1) / (sqrtf(v * c2) + 1e-8f);
-    }
-    __syncthreads();
-    if (tid == 0) *a.step = t;
 }
 
 // Inference: each wavefront evaluates samples s = wave, wave + waves, ...
@@ -176,6 +231,22 @@ __global__ __launch_bounds__(256) void k_mlp_infer(MlpArgs a) {
 
 namespace mxn {
 
+// Gradient rows for calls on the context's stream.  Each stream has its own, so calls on different streams
+// do not share memory; null (the one-workgroup kernel runs) while the stream is being captured, whose replays
+// could overlap other calls, for a fifth stream, and without memory.
+static float *mlp_scratch(nb_ctx *ctx, nb_mlp *mlp) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return nullptr;
+    for (nb_mlp::Scratch &e : mlp->scratch) {
+        if (!e.buf.p) {
+            if (ensure(ctx, e.buf, sizeof(float) * kMlpRow * kMlpParts) != NB_OK) return nullptr;
+            e.stream = ctx->stream;
+        }
+        if (e.stream == ctx->stream) return (float *)e.buf.p;
+    }
+    return nullptr;
+}
+
 int launch_mlp_step(nb_ctx *ctx, nb_mlp *mlp, const float *X, const float *y, int batch, float lr, float *loss,
                     float *grad_out) {
     MlpArgs a{};
@@ -191,7 +262,17 @@ int launch_mlp_step(nb_ctx *ctx, nb_mlp *mlp, const float *X, const float *y, in
     a.lr = lr;
     a.loss = loss;
     a.grad_out = grad_out;
-    k_mlp_step<<<1, 256, 0, ctx->stream>>>(a);
+    // Two samples per wavefront or fewer: the second launch costs more than the chains it shortens.
+    const int nparts = batch <= 8 ? 1 : std::min((batch + 3) / 4, kMlpParts);
+    // the launches of two threads that use one model do not interleave
+    std::lock_guard<std::mutex> lock(mlp->mu);
+    if (nparts > 1) a.parts = mlp_scratch(ctx, mlp);
+    if (!a.parts) {
+        k_mlp_step<false><<<1, 256, 0, ctx->stream>>>(a);
+    } else {
+        k_mlp_step<true><<<nparts, 256, 0, ctx->stream>>>(a);
+        k_mlp_finish<<<(NPARAM + 1 + 63) / 64, 256, 0, ctx->stream>>>(a, nparts);
+    }
     MXN_HIP(hipGetLastError());
     return NB_OK;
 }
