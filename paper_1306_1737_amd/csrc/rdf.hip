@@ -6,17 +6,25 @@
 //
 // Work items as in the force kernel: a wavefront takes entries of one
 // i-cluster, a lane one j-particle of one entry, and loops over the M
-// i-particles (scalar registers).  Every lane forms its squared distance and
-// bin without branching; only the count itself is predicated (real, active
-// pair below r_max).  Counts go to a per-workgroup LDS histogram, flushed
-// once with 64-bit atomics; integer sums, so the result is exact.
+// i-particles (scalar registers).  A pair below r_max is counted in a
+// per-workgroup LDS histogram (rows by ordered type pair, folded onto the
+// unordered one at the end), flushed once with 64-bit atomics; integer sums,
+// so the result is exact.
 //
 // The bin is decided in FP32 from r2 alone: e_k = (float)((k dr)^2) in FP64,
-// bin k the largest with e_k <= r2 (a sqrt guess corrected by one step each
-// way).  r2 is formed as the search forms its particle test (j moved back by
-// the entry's image shift, separately rounded operations; this file is
-// compiled with -ffp-contract=off).
+// bin k the largest with e_k <= r2.  t = sqrt(r2)/dr from the hardware square
+// root is within a few 1e-7 t of the exact quotient, and an edge within 1e-7 k
+// of k, so the integer part of t is that bin unless t lies within `near` of an
+// integer; only then are the edges themselves read.  r2 is formed as the
+// search forms its particle test (j moved back by the entry's image shift,
+// separately rounded operations; this file is compiled with
+// -ffp-contract=off).
+//
+// Bound: VALU issue (about 22 instructions per listed pair, 64 with an IEEE
+// square root and both edges read for every pair) and the flush, whose
+// atomics grow with the number of workgroups: hence eight wavefronts to one.
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "internal.h"
@@ -33,32 +41,42 @@ struct RdfArgs {
     const float *edge;      // nbins + 1 squared bin edges
     unsigned long long *hist;
     int nbins, nt, skip_excl;
-    float inv_dr;
+    float inv_dr, near;
 };
 
+constexpr int kRdfWaves = 8;   // wavefronts per workgroup (three to a CU fit: scalar registers)
+
+// The exact bin of a pair whose t lies next to an integer.
+__device__ inline int edge_bin(const float *edge, int nbins, float inv_dr, float r2) {
+    int bin = (int)(sqrtf(r2) * inv_dr);   // also for an r2 the hardware root flushes to zero
+    bin = bin > nbins - 1 ? nbins - 1 : bin;
+    bin -= bin > 0 && edge[bin] > r2 ? 1 : 0;
+    bin += (bin + 1 < nbins && !(edge[bin + 1] > r2)) ? 1 : 0;
+    return bin;
+}
+
 template <int M, int N>
-__global__ __launch_bounds__(256) void k_rdf(RdfArgs a) {
+__global__ __launch_bounds__(64 * kRdfWaves) void k_rdf(RdfArgs a) {
     constexpr int B = 64 / N;
     constexpr unsigned FULL = (1u << M) - 1u;
     extern __shared__ float4 smem[];
     float4 *svec = smem;                                         // 27 image shift vectors
-    float *edge = reinterpret_cast<float *>(smem + 32);          // nbins + 1
-    unsigned *h = reinterpret_cast<unsigned *>(edge + a.nbins + 1);
+    unsigned *h = reinterpret_cast<unsigned *>(smem + 32);
     const int nh = a.nt * a.nt * a.nbins;
     for (int t = threadIdx.x; t < 27; t += blockDim.x) svec[t] = a.shiftvec[t];
-    for (int t = threadIdx.x; t <= a.nbins; t += blockDim.x) edge[t] = a.edge[t];
     for (int t = threadIdx.x; t < nh; t += blockDim.x) h[t] = 0u;
     __syncthreads();
-    const float r2max = edge[a.nbins];
+    const float r2max = a.edge[a.nbins];
     const long total = a.totals[2];
     const int lane = threadIdx.x & 63, jb = lane % N, eo = lane / N;
-    for (long item = (long)blockIdx.x * 4 + (threadIdx.x >> 6); item < total; item += (long)gridDim.x * 4) {
+    for (long item = (long)blockIdx.x * kRdfWaves + (threadIdx.x >> 6); item < total;
+         item += (long)gridDim.x * kRdfWaves) {
         const int4 it = a.items[item];
         const int ci = __builtin_amdgcn_readfirstlane(it.x);
         const int js = __builtin_amdgcn_readfirstlane(it.y);
         const int je = __builtin_amdgcn_readfirstlane(it.z);
         float xi[M], yi[M], zi[M];
-        int ti[M];
+        int ti[M];   // histogram row of the i-particle's type
         unsigned ireal = 0;
 #pragma unroll
         for (int k = 0; k < M; ++k) {
@@ -66,8 +84,9 @@ __global__ __launch_bounds__(256) void k_rdf(RdfArgs a) {
             xi[k] = p.x; yi[k] = p.y; zi[k] = p.z;
             const int t = a.type_s[ci * M + k];
             ireal |= (t >= 0 ? 1u : 0u) << k;
-            ti[k] = t < 0 ? 0 : (t >= a.nt ? a.nt - 1 : t);
+            ti[k] = (t < 0 ? 0 : (t >= a.nt ? a.nt - 1 : t)) * a.nt * a.nbins;
         }
+        ireal = __builtin_amdgcn_readfirstlane(ireal);
         for (int e0 = js; e0 < je; e0 += B) {
             const int e = e0 + eo;
             const bool valid = e < je;
@@ -75,7 +94,7 @@ __global__ __launch_bounds__(256) void k_rdf(RdfArgs a) {
             const int jslot = en.cj * N + jb;
             const float4 pj = a.xs_now[jslot];
             const int tjr = a.type_s[jslot];
-            const int tj = tjr < 0 ? 0 : (tjr >= a.nt ? a.nt - 1 : tjr);
+            const int tj = (tjr < 0 ? 0 : (tjr >= a.nt ? a.nt - 1 : tjr)) * a.nbins;
             const float4 sv = svec[en.shift];
             const float xj = pj.x - sv.x, yj = pj.y - sv.y, zj = pj.z - sv.z;
             const unsigned long long m64 = ((unsigned long long)en.mhi << 32) | en.mlo;
@@ -87,22 +106,30 @@ __global__ __launch_bounds__(256) void k_rdf(RdfArgs a) {
             }
             if (a.skip_excl) act &= mb;
             if (!valid || tjr < 0) act = 0u;
+            const float lim = act ? r2max : -1.0f;
+            auto pairs = [&](auto whole) {   // whole: every lane takes all M i-particles or none
 #pragma unroll
-            for (int k = 0; k < M; ++k) {
-                const float dx = xi[k] - xj, dy = yi[k] - yj, dz = zi[k] - zj;
-                const float r2 = (dx * dx + dy * dy) + dz * dz;
-                int bin = (int)(sqrtf(r2) * a.inv_dr);
-                bin = bin < 0 ? 0 : (bin > a.nbins - 1 ? a.nbins - 1 : bin);
-                bin -= edge[bin] > r2 ? 1 : 0;
-                bin += (bin + 1 < a.nbins && !(edge[bin + 1] > r2)) ? 1 : 0;
-                const int lo = ti[k] < tj ? ti[k] : tj, hi = ti[k] < tj ? tj : ti[k];
-                if (((act >> k) & 1u) && r2 < r2max) atomicAdd(h + (lo * a.nt + hi) * a.nbins + bin, 1u);
-            }
+                for (int k = 0; k < M; ++k) {
+                    const float dx = xi[k] - xj, dy = yi[k] - yj, dz = zi[k] - zj;
+                    const float r2 = (dx * dx + dy * dy) + dz * dz;
+                    if (r2 < lim && (whole || ((act >> k) & 1u))) {
+                        const float t = __builtin_amdgcn_sqrtf(r2) * a.inv_dr;
+                        int bin = (int)t;
+                        if (fabsf(t - rintf(t)) < a.near) bin = edge_bin(a.edge, a.nbins, a.inv_dr, r2);
+                        atomicAdd(h + ti[k] + tj + bin, 1u);
+                    }
+                }
+            };
+            if (__ballot(act != 0u && act != FULL) == 0ull) pairs(std::true_type{});
+            else pairs(std::false_type{});
         }
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < nh; t += blockDim.x)
-        if (h[t]) atomicAdd(a.hist + t, (unsigned long long)h[t]);
+    for (int t = threadIdx.x; t < nh; t += blockDim.x) {   // type pair (p, q) counts under (min, max)
+        const unsigned c = h[t];
+        const int row = t / a.nbins, p = row / a.nt, q = row % a.nt;
+        if (c) atomicAdd(a.hist + (p <= q ? t : (q * a.nt + p) * a.nbins + t % a.nbins), (unsigned long long)c);
+    }
 }
 
 }  // namespace
@@ -139,14 +166,15 @@ int launch_rdf(nb_ctx *ctx, const nb_grid *g, const nb_list *l, float r_max, int
     a.nt = nt;
     a.skip_excl = skip_excl;
     a.inv_dr = (float)((double)nbins / (double)r_max);
-    // persistent workgroups: enough to fill the GPU, each flushes its histogram once
-    const long need = (l->cap_items + 3) / 4;
-    const int nb = (int)std::max(1L, std::min(need, 2048L));
+    a.near = 1e-6f * (float)(nbins + 1);   // t <= nbins up to rounding
+    // persistent workgroups, three to a CU; each flushes its histogram once
+    const long need = (std::min(l->cap_items, l->est_items + l->est_items / 4 + 256) + kRdfWaves - 1) / kRdfWaves;
+    const int nb = (int)std::max(1L, std::min(need, 768L));
     const size_t lds = rdf_lds_bytes(nbins, nt);
-    if (g->m == 4 && g->nn == 4) k_rdf<4, 4><<<nb, 256, lds, st>>>(a);
-    else if (g->m == 4 && g->nn == 8) k_rdf<4, 8><<<nb, 256, lds, st>>>(a);
-    else if (g->m == 8 && g->nn == 4) k_rdf<8, 4><<<nb, 256, lds, st>>>(a);
-    else k_rdf<8, 8><<<nb, 256, lds, st>>>(a);
+    if (g->m == 4 && g->nn == 4) k_rdf<4, 4><<<nb, 64 * kRdfWaves, lds, st>>>(a);
+    else if (g->m == 4 && g->nn == 8) k_rdf<4, 8><<<nb, 64 * kRdfWaves, lds, st>>>(a);
+    else if (g->m == 8 && g->nn == 4) k_rdf<8, 4><<<nb, 64 * kRdfWaves, lds, st>>>(a);
+    else k_rdf<8, 8><<<nb, 64 * kRdfWaves, lds, st>>>(a);
     MXN_HIP(hipGetLastError());
     return NB_OK;
 }
