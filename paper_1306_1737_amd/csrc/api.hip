@@ -65,6 +65,18 @@ void release(DevBuf &b) {
     b.mem.reset();
 }
 
+void *StreamScratch::get(const nb_ctx *c, size_t bytes) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return nullptr;
+    for (Entry &e : entry) {
+        if (e.buf.p && e.stream != c->stream) continue;
+        if (ensure(c, e.buf, bytes) != NB_OK) return nullptr;
+        e.stream = c->stream;
+        return e.buf.p;
+    }
+    return nullptr;
+}
+
 static hipEvent_t take_event(nb_ctx *c) {
     if (!c->event_pool.empty()) {
         hipEvent_t e = c->event_pool.back();
@@ -174,6 +186,7 @@ void nb_destroy(nb_ctx *c) {
     release(c->blockpart);
     release(c->etab);
     release(c->rdf_edge);
+    c->rdf_parts.clear();
     release(c->mlp_io);
     release(c->stats_buf);
     release(c->flags_buf);
@@ -1179,7 +1192,7 @@ void nb_mlp_free(nb_mlp *m) {
     if (m->ctx->mlp == m) m->ctx->mlp = nullptr;
     DevBuf *bufs[] = {&m->params, &m->m, &m->v, &m->step, &m->lo, &m->hi};
     for (DevBuf *b : bufs) release(*b);
-    for (nb_mlp::Scratch &e : m->scratch) release(e.buf);
+    m->scratch.clear();
     delete m;
 }
 

@@ -58,6 +58,25 @@ struct DevBuf {
 int ensure(const ::nb_ctx *c, DevBuf &b, size_t bytes);
 void release(DevBuf &b);
 
+// Scratch that one launch of a call fills and its next launch reads.  Each
+// stream has a buffer of its own, so calls on different streams do not share
+// memory, and a call holds mu over its launches, so those of two threads do
+// not interleave.  get() gives null, and the caller takes its one-launch form,
+// while the context's stream is being captured (replays could overlap other
+// calls), for a fifth stream, and without memory.
+struct StreamScratch {
+    struct Entry {
+        hipStream_t stream = nullptr;
+        DevBuf buf;
+    };
+    Entry entry[4];
+    std::mutex mu;
+    void *get(const ::nb_ctx *c, size_t bytes);   // mu held
+    void clear() {
+        for (Entry &e : entry) release(e.buf);
+    }
+};
+
 }  // namespace mxn
 
 // Cluster-pair list entry as the kernels use it (16 bytes): j-cluster, image
@@ -85,6 +104,7 @@ struct nb_ctx {
     mxn::DevBuf blockpart;      // sums of the partials over contiguous shares of the work items
     mxn::DevBuf etab;           // Ewald table of the tabulated Coulomb variant
     mxn::DevBuf rdf_edge;       // squared bin edges of the pair distance histogram
+    mxn::StreamScratch rdf_parts;   // histograms of the workgroups
     float rdf_rmax = -1.0f;
     int rdf_nbins = 0;
     float etab_beta = -1.0f, etab_rc = -1.0f;
@@ -196,13 +216,7 @@ struct nb_mlp {
     double dom_target = 0, dom_dt = 0, dom_brc = 0;
     int dom_ntypes = 0;
     std::vector<double> dom_charge, dom_c6c12;
-    // gradient rows of a spread minibatch, one buffer per stream that trained the model
-    struct Scratch {
-        hipStream_t stream = nullptr;
-        mxn::DevBuf buf;
-    };
-    Scratch scratch[4];
-    std::mutex mu;   // a training call's two launches stay together
+    mxn::StreamScratch scratch;   // gradient rows of a spread minibatch
 };
 
 namespace mxn {

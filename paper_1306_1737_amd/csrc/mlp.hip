@@ -231,22 +231,6 @@ __global__ __launch_bounds__(256) void k_mlp_infer(MlpArgs a) {
 
 namespace mxn {
 
-// Gradient rows for calls on the context's stream.  Each stream has its own, so calls on different streams
-// do not share memory; null (the one-workgroup kernel runs) while the stream is being captured, whose replays
-// could overlap other calls, for a fifth stream, and without memory.
-static float *mlp_scratch(nb_ctx *ctx, nb_mlp *mlp) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(ctx->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return nullptr;
-    for (nb_mlp::Scratch &e : mlp->scratch) {
-        if (!e.buf.p) {
-            if (ensure(ctx, e.buf, sizeof(float) * kMlpRow * kMlpParts) != NB_OK) return nullptr;
-            e.stream = ctx->stream;
-        }
-        if (e.stream == ctx->stream) return (float *)e.buf.p;
-    }
-    return nullptr;
-}
-
 int launch_mlp_step(nb_ctx *ctx, nb_mlp *mlp, const float *X, const float *y, int batch, float lr, float *loss,
                     float *grad_out) {
     MlpArgs a{};
@@ -264,9 +248,8 @@ int launch_mlp_step(nb_ctx *ctx, nb_mlp *mlp, const float *X, const float *y, in
     a.grad_out = grad_out;
     // Two samples per wavefront or fewer: the second launch costs more than the chains it shortens.
     const int nparts = batch <= 8 ? 1 : std::min((batch + 3) / 4, kMlpParts);
-    // the launches of two threads that use one model do not interleave
-    std::lock_guard<std::mutex> lock(mlp->mu);
-    if (nparts > 1) a.parts = mlp_scratch(ctx, mlp);
+    std::lock_guard<std::mutex> lock(mlp->scratch.mu);
+    if (nparts > 1) a.parts = (float *)mlp->scratch.get(ctx, sizeof(float) * kMlpRow * kMlpParts);
     if (!a.parts) {
         k_mlp_step<false><<<1, 256, 0, ctx->stream>>>(a);
     } else {

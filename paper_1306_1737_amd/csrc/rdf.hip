@@ -8,21 +8,22 @@
 // i-cluster, a lane one j-particle of one entry, and loops over the M
 // i-particles (scalar registers).  A pair below r_max is counted in a
 // per-workgroup LDS histogram (rows by ordered type pair, folded onto the
-// unordered one at the end), flushed once with 64-bit atomics; integer sums,
-// so the result is exact.
+// unordered one at the end); integer sums, so the result is exact.
 //
 // The bin is decided in FP32 from r2 alone: e_k = (float)((k dr)^2) in FP64,
 // bin k the largest with e_k <= r2.  t = sqrt(r2)/dr from the hardware square
-// root is within a few 1e-7 t of the exact quotient, and an edge within 1e-7 k
-// of k, so the integer part of t is that bin unless t lies within `near` of an
+// root is within 2.4e-7 t of the exact quotient, and an edge within 3e-8 k of k,
+// so the integer part of t is that bin unless t lies within `near` of an
 // integer; only then are the edges themselves read.  r2 is formed as the
 // search forms its particle test (j moved back by the entry's image shift,
 // separately rounded operations; this file is compiled with
 // -ffp-contract=off).
 //
-// Bound: VALU issue (about 22 instructions per listed pair, 64 with an IEEE
-// square root and both edges read for every pair) and the flush, whose
-// atomics grow with the number of workgroups: hence eight wavefronts to one.
+// Bound: VALU issue (26 instructions per listed pair, 64 with an IEEE square
+// root and both edges read for every pair), 57 us of the 96 000-atom frame
+// (113 us before), and the workgroups' histograms: flushed with global atomics
+// by 768 workgroups they took 25 us, written to scratch and summed by a second
+// launch 5 us.
 #include <cmath>
 #include <type_traits>
 #include <vector>
@@ -40,10 +41,12 @@ struct RdfArgs {
     const float4 *shiftvec;
     const float *edge;      // nbins + 1 squared bin edges
     unsigned long long *hist;
+    unsigned *parts;        // histogram of each workgroup (null: counts go to hist at once)
     int nbins, nt, skip_excl;
     float inv_dr, near;
 };
 
+constexpr int kRdfGroups = 768;   // most workgroups of a call
 constexpr int kRdfWaves = 8;   // wavefronts per workgroup (three to a CU fit: scalar registers)
 
 // The exact bin of a pair whose t lies next to an integer.
@@ -55,18 +58,26 @@ __device__ inline int edge_bin(const float *edge, int nbins, float inv_dr, float
     return bin;
 }
 
+// Counts of bin t of the ordered type pair (p, q) go to the pair (min, max).
+__device__ inline void add_count(const RdfArgs &a, int t, unsigned long long c) {
+    const int row = t / a.nbins, p = row / a.nt, q = row % a.nt;
+    if (c) atomicAdd(a.hist + (p <= q ? t : (q * a.nt + p) * a.nbins + t % a.nbins), c);
+}
+
 template <int M, int N>
 __global__ __launch_bounds__(64 * kRdfWaves) void k_rdf(RdfArgs a) {
     constexpr int B = 64 / N;
     constexpr unsigned FULL = (1u << M) - 1u;
     extern __shared__ float4 smem[];
     float4 *svec = smem;                                         // 27 image shift vectors
-    unsigned *h = reinterpret_cast<unsigned *>(smem + 32);
+    float *edge = reinterpret_cast<float *>(smem + 32);          // nbins + 1
+    unsigned *h = reinterpret_cast<unsigned *>(edge + a.nbins + 1);
     const int nh = a.nt * a.nt * a.nbins;
     for (int t = threadIdx.x; t < 27; t += blockDim.x) svec[t] = a.shiftvec[t];
+    for (int t = threadIdx.x; t <= a.nbins; t += blockDim.x) edge[t] = a.edge[t];
     for (int t = threadIdx.x; t < nh; t += blockDim.x) h[t] = 0u;
     __syncthreads();
-    const float r2max = a.edge[a.nbins];
+    const float r2max = edge[a.nbins];
     const long total = a.totals[2];
     const int lane = threadIdx.x & 63, jb = lane % N, eo = lane / N;
     for (long item = (long)blockIdx.x * kRdfWaves + (threadIdx.x >> 6); item < total;
@@ -115,7 +126,7 @@ __global__ __launch_bounds__(64 * kRdfWaves) void k_rdf(RdfArgs a) {
                     if (r2 < lim && (whole || ((act >> k) & 1u))) {
                         const float t = __builtin_amdgcn_sqrtf(r2) * a.inv_dr;
                         int bin = (int)t;
-                        if (fabsf(t - rintf(t)) < a.near) bin = edge_bin(a.edge, a.nbins, a.inv_dr, r2);
+                        if (fabsf(t - rintf(t)) < a.near) bin = edge_bin(edge, a.nbins, a.inv_dr, r2);
                         atomicAdd(h + ti[k] + tj + bin, 1u);
                     }
                 }
@@ -125,11 +136,30 @@ __global__ __launch_bounds__(64 * kRdfWaves) void k_rdf(RdfArgs a) {
         }
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < nh; t += blockDim.x) {   // type pair (p, q) counts under (min, max)
-        const unsigned c = h[t];
-        const int row = t / a.nbins, p = row / a.nt, q = row % a.nt;
-        if (c) atomicAdd(a.hist + (p <= q ? t : (q * a.nt + p) * a.nbins + t % a.nbins), (unsigned long long)c);
+    if (a.parts) {
+        unsigned *row = a.parts + (size_t)blockIdx.x * nh;
+        for (int t = threadIdx.x; t < nh; t += blockDim.x) row[t] = h[t];
+    } else {
+        for (int t = threadIdx.x; t < nh; t += blockDim.x) add_count(a, t, h[t]);
     }
+}
+
+// Sum of the workgroups' histograms: a workgroup takes 64 bins (x) of an eighth of the rows (y), each of its 16
+// wavefronts every 16th of those rows.
+constexpr int kRdfShares = 8;
+__global__ __launch_bounds__(1024) void k_rdf_sum(RdfArgs a, int nparts) {
+    __shared__ unsigned long long red[16][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nh = a.nt * a.nt * a.nbins, t = blockIdx.x * 64 + lane;
+    unsigned long long s = 0;
+    if (t < nh) {
+#pragma unroll 8
+        for (int k = blockIdx.y * 16 + w; k < nparts; k += 16 * kRdfShares) s += a.parts[(size_t)k * nh + t];
+    }
+    red[w][lane] = s;
+    __syncthreads();
+    if (w > 0 || t >= nh) return;
+    for (int k = 1; k < 16; ++k) s += red[k][lane];
+    add_count(a, t, s);
 }
 
 }  // namespace
@@ -166,15 +196,21 @@ int launch_rdf(nb_ctx *ctx, const nb_grid *g, const nb_list *l, float r_max, int
     a.nt = nt;
     a.skip_excl = skip_excl;
     a.inv_dr = (float)((double)nbins / (double)r_max);
-    a.near = 1e-6f * (float)(nbins + 1);   // t <= nbins up to rounding
+    a.near = 4e-7f * (float)(nbins + 1);   // t <= nbins up to rounding; relative errors: root 1.2e-7, 1/dr and the
+                                           // product 6e-8 each, an edge 3e-8
     // persistent workgroups, three to a CU; each flushes its histogram once
     const long need = (std::min(l->cap_items, l->est_items + l->est_items / 4 + 256) + kRdfWaves - 1) / kRdfWaves;
-    const int nb = (int)std::max(1L, std::min(need, 768L));
+    const int nb = (int)std::max(1L, std::min(need, (long)kRdfGroups));
     const size_t lds = rdf_lds_bytes(nbins, nt);
+    std::lock_guard<std::mutex> lock(ctx->rdf_parts.mu);
+    // A workgroup's atomics take about 32 ns (1500 counted bins, 46 G atomics/s over the whole chip, wherever they
+    // go), the summing launch about 5 us.
+    if (nb > 128) a.parts = (unsigned *)ctx->rdf_parts.get(ctx, (size_t)nt * nt * nbins * kRdfGroups * sizeof(unsigned));
     if (g->m == 4 && g->nn == 4) k_rdf<4, 4><<<nb, 64 * kRdfWaves, lds, st>>>(a);
     else if (g->m == 4 && g->nn == 8) k_rdf<4, 8><<<nb, 64 * kRdfWaves, lds, st>>>(a);
     else if (g->m == 8 && g->nn == 4) k_rdf<8, 4><<<nb, 64 * kRdfWaves, lds, st>>>(a);
     else k_rdf<8, 8><<<nb, 64 * kRdfWaves, lds, st>>>(a);
+    if (a.parts) k_rdf_sum<<<dim3((nt * nt * nbins + 63) / 64, kRdfShares), 1024, 0, st>>>(a, nb);
     MXN_HIP(hipGetLastError());
     return NB_OK;
 }

@@ -48,3 +48,38 @@ def test_bins_at_edges(shape, nbins, r_max):
         mxn.nb_grid_free(g)
     finally:
         mxn.nb_destroy(ctx)
+
+
+def test_many_workgroups_and_capture():
+    """A box large enough for the summing launch, and the same call captured (which flushes directly)."""
+    import torch
+    import synth
+    import paper_1306_1737_amd as mxn
+    box = synth.water_box(12000, synth.box_edge_for(12000), seed=5)
+    dev = torch.device("cuda:0")
+    ctx = mxn.nb_create(0)
+    try:
+        xq, ty = torch.from_numpy(box.xyzq()).to(dev), torch.from_numpy(box.type).to(dev)
+        eo, ei = torch.from_numpy(box.excl_off).to(dev), torch.from_numpy(box.excl_idx).to(dev)
+        g = mxn.nb_grid_sort(ctx, box.box, xq, ty, (8, 8))
+        lst = mxn.nb_pairlist_build(ctx, g, 1.01, 1.01, eo, ei)
+        hist = torch.zeros(4 * 300, dtype=torch.int64, device=dev)
+        mxn.nb_rdf(ctx, g, lst, xq, 1.0, 300, 2, hist)
+        mxn.nb_sync(ctx)
+        once = hist.clone()
+        # every pair below r_max, as the list's own statistics count them
+        assert int(once.sum()) == sum(mxn.nb_list_stats(ctx, g, lst, xq, 1.0)[2:])
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            mxn.nb_set_stream(ctx)
+            mxn.nb_rdf(ctx, g, lst, xq, 1.0, 300, 2, hist)
+        mxn.nb_set_stream(ctx)
+        for k in range(3):
+            graph.replay()
+            mxn.nb_rdf(ctx, g, lst, xq, 1.0, 300, 2, hist)   # eager work between the replays
+            torch.cuda.synchronize()
+            assert (hist == (2 * k + 3) * once).all()
+        mxn.nb_list_free(lst)
+        mxn.nb_grid_free(g)
+    finally:
+        mxn.nb_destroy(ctx)
