@@ -95,24 +95,56 @@ __device__ inline int lower_bound(int lo, int hi, F key, float v) {
     return lo;
 }
 
-// Candidates are handled one per lane: a lane owning a candidate j-cluster
-// outside the rBB shortcut checks its M x N particle pairs itself (all loads
-// independent, early exit on the first pair within rlist), and in the fill
-// pass builds the interaction mask of an accepted candidate from the
-// particles' realness, the self-pair triangle and the i-cluster's exclusions
-// (their partners' slots and positions staged in LDS once per wavefront).
-// a.parts wavefronts share an i-cluster: part p takes the p-th contiguous
-// share of every image shift's candidate columns.
-constexpr int kExclStage = 64;   // staged exclusion partners per wavefront, one per lane
-static_assert(kExclStage <= 64, "a lane stages one partner");
+// inclusive sum over the lanes at and below this one (DPP row shifts, then row broadcasts)
+__device__ inline int lane_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, true);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+__device__ inline float lane_value(float x, int lane) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+// orders a wavefront's LDS writes before its reads by other lanes
+__device__ inline void lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One wavefront per (i-cluster, part): a.parts wavefronts share an i-cluster,
+// part p takes the p-th contiguous share of every image shift's candidate
+// columns.  Bound by VALU issue (4.8 k instructions per wavefront and 110 us on
+// the 96 000-atom 8x8 list when every lane checked its own candidate), hence:
+//   - Lane s works out image shift s's candidate columns; only shifts that
+//     have any are walked (one, for a cluster away from the faces).  For the
+//     zero shift columns before the i-cluster's own hold nothing of the half
+//     list and are left out, and so are earlier clusters of a window.
+//   - Lanes own candidate columns (binary search of the z window), then, after
+//     a scan flattens the windows, candidate j-clusters (box test).
+//   - The particle check of the candidates outside the rBB shortcut is taken
+//     by all lanes together: the candidates are queued in LDS and 64/N of them
+//     are checked at a time, lane = (candidate, j-particle), the M i-particles
+//     in scalar registers.  Each loads one coalesced 16 N-byte run per
+//     candidate instead of N scattered particles per lane.
+//   - In the fill pass lane q holds exclusion partner q of the i-particles; it
+//     finds its own candidate among the flattened windows and clears its mask
+//     bit through LDS, so no candidate loops over the partners.
+// More partners than lanes: each accepted candidate reads them from the CSR.
+constexpr int kExclStage = 64;   // exclusion partners held, one per lane
 
 template <int M, int N, bool FILL, class A>
 __device__ inline void search_body(const A &a, int blk) {
     constexpr unsigned FULL = (1u << M) - 1u;
-    __shared__ float4 xpos[4][kExclStage];
-    __shared__ float4 ipos[4][M];   // the i-cluster's particles moved by the current image shift
+    constexpr int G = 64 / N;   // candidates per step of the particle check
+    __shared__ unsigned queue[4][64];             // candidates to check: cj * 16 + real slots
+    __shared__ unsigned long long mexcl[4][64];   // a batch's masks while partners clear bits
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int gw = blk * 4 + w;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const int gw = __builtin_amdgcn_readfirstlane(blk * 4 + w);
     const int P = a.parts, ci = gw / P, part = gw % P;
     if (ci >= a.nci_cap) return;
     const int nci = *a.nslots / M;
@@ -127,17 +159,19 @@ __device__ inline void search_body(const A &a, int blk) {
     }
     const float4 lo = ld(a.bbi_lo + ci), hi = ld(a.bbi_hi + ci);
     // the i-cluster's real slots: the mask the grid sort stores in its box's lo.w
-    const unsigned ireal = __float_as_uint(lo.w);
+    const unsigned ireal = __builtin_amdgcn_readfirstlane(__float_as_uint(lo.w));
     // keeps the z windows conservative against rounding: the FP32 squared distances
     // carry a relative error below 1e-6, so sqrt of that error is below 1e-3 rlist
     const float zmargin = 1e-3f + 2e-3f * a.rlist;
-    const float pmargin = 1e-3f;   // keeps the particle-to-box prefilter conservative
-    const float rp2 = (a.rlist + pmargin) * (a.rlist + pmargin);
-    // exclusion partners of the i-particles: (slot * 8 + i-index, position), staged in LDS
-    int nexcl = 0;
+    auto col_x = [&](float x) { return max(0, min((int)floorf(x * a.inv_x), a.nx - 1)); };   // as the grid sort
+    auto col_y = [&](float y) { return max(0, min((int)floorf(y * a.inv_y), a.ny - 1)); };
+    // lane k < M: i-particle k (a dummy's NaN fails every distance test)
+    float4 pi = ld(a.xs + ci * M + (lane < M ? lane : 0));
+    if (!((ireal >> (lane & (M - 1))) & 1u)) pi.x = __builtin_nanf("");
+    // lane q < nexcl: exclusion partner q as slot * 8 + i-index, its position and column
+    int nexcl = 0, xv = 0, xcol_x = -1, xcol_y = -1;
     bool staged = true;
-    int xlo = 0x7fffffff, xhi = -1;   // slot range of the staged partners
-    int xv = 0;                       // lane q < nexcl: staged partner q as slot * 8 + i-index
+    float4 xp = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (FILL) {
         int e0 = 0, e1 = 0;
         if (lane < M && ((ireal >> lane) & 1u)) {
@@ -145,216 +179,196 @@ __device__ inline void search_body(const A &a, int blk) {
             e0 = a.excl_off[io];
             e1 = a.excl_off[io + 1];
         }
-        int incl = e1 - e0;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += v;
-        }
+        const int incl = lane_scan(e1 - e0);
         nexcl = __builtin_amdgcn_readlane(incl, 63);
         staged = nexcl <= kExclStage && (long)a.nci_cap * M < (1L << 28);   // slot * 8 + i-index fits an int
         if (staged) {
-            // partner q of the i-cluster goes to lane q: its i-particle is the first whose inclusive
-            // count exceeds q, so every lane issues its own load chain at once
+            // partner q's i-particle is the first whose inclusive count exceeds q, so every lane issues its
+            // own load chain at once
             int ia = 0, first = 0;
 #pragma unroll
             for (int k = 0; k < M - 1; ++k) {
-                const int ik = __shfl(incl, k, 64);
+                const int ik = __builtin_amdgcn_readlane(incl, k);
                 if (lane >= ik) { ia = k + 1; first = ik; }
             }
             const int e = __shfl(e0, ia, 64) + lane - first;
             if (lane < nexcl) {
                 const int ps = a.slot_of[a.excl_idx[e]];
                 xv = ps * 8 + ia;
-                xpos[w][lane] = ld(a.xs + ps);
-                xlo = ps;
-                xhi = ps;
+                xp = ld(a.xs + ps);
+                xcol_x = col_x(xp.x);
+                xcol_y = col_y(xp.y);
             }
         }
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            xlo = min(xlo, __shfl_xor(xlo, o, 64));
-            xhi = max(xhi, __shfl_xor(xhi, o, 64));
-        }
-        xlo = __builtin_amdgcn_readfirstlane(xlo);
-        xhi = __builtin_amdgcn_readfirstlane(xhi);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
+    // lane s: image shift s and its candidate columns, a superset with one column of margin against rounding
+    const float sx_l = (float)(lane / 9 - 1) * a.Lx, sy_l = (float)((lane / 3) % 3 - 1) * a.Ly,
+                sz_l = (float)(lane % 3 - 1) * a.Lz;
+    int cx0_l = max(0, (int)floorf((lo.x + sx_l - a.rlist) * a.inv_x) - 1);
+    const int cx1_l = min(a.nx - 1, (int)floorf((hi.x + sx_l + a.rlist) * a.inv_x) + 1);
+    const int cy0_l = max(0, (int)floorf((lo.y + sy_l - a.rlist) * a.inv_y) - 1);
+    const int cy1_l = min(a.ny - 1, (int)floorf((hi.y + sy_l + a.rlist) * a.inv_y) + 1);
+    if (lane == 13) cx0_l = max(cx0_l, col_x(lo.x));   // the own column's row: earlier ones precede it in slot order
+    // wrapped particles lie in [0, L): no z window can be hit from beyond that range
+    const bool any = lane >= 13 && lane < 27 && cx0_l <= cx1_l && cy0_l <= cy1_l &&
+                     !(lo.z + sz_l - a.rlist - zmargin > a.Lz + zmargin || hi.z + sz_l + a.rlist + zmargin < -zmargin);
     int cnt = 0;
-    if (lo.x <= hi.x) {   // the cluster holds real particles
-        for (int s = 13; s < 27; ++s) {
-            const float sx = (float)(s / 9 - 1) * a.Lx, sy = (float)((s / 3) % 3 - 1) * a.Ly,
-                        sz = (float)(s % 3 - 1) * a.Lz;
-            const float slx = lo.x + sx, shx = hi.x + sx, sly = lo.y + sy, shy = hi.y + sy, slz = lo.z + sz,
-                        shz = hi.z + sz;
-            // candidate columns: a superset, one column of margin against rounding
-            int cx0 = (int)floorf((slx - a.rlist) * a.inv_x) - 1, cx1 = (int)floorf((shx + a.rlist) * a.inv_x) + 1;
-            int cy0 = (int)floorf((sly - a.rlist) * a.inv_y) - 1, cy1 = (int)floorf((shy + a.rlist) * a.inv_y) + 1;
-            cx0 = cx0 < 0 ? 0 : cx0; cy0 = cy0 < 0 ? 0 : cy0;
-            cx1 = cx1 > a.nx - 1 ? a.nx - 1 : cx1; cy1 = cy1 > a.ny - 1 ? a.ny - 1 : cy1;
-            if (cx0 > cx1 || cy0 > cy1) continue;
-            // wrapped particles lie in [0, L): no z window can be hit from beyond that range
-            if (slz - a.rlist - zmargin > a.Lz + zmargin || shz + a.rlist + zmargin < -zmargin) continue;
-            // shifted i-particles, in LDS (read back as broadcasts; registers would cost occupancy)
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the previous shift's reads are done
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (lane < M) {
-                const float4 p = ld(a.xs + ci * M + lane);
-                ipos[w][lane] = make_float4(p.x + sx, p.y + sy, p.z + sz, 0.0f);
+    // an i-cluster of padding only has no real particles (and an empty box)
+    for (unsigned long long shifts = lo.x <= hi.x ? __ballot(any) : 0ull; shifts; shifts &= shifts - 1ull) {
+        const int s = __builtin_ctzll(shifts);
+        const float sx = lane_value(sx_l, s), sy = lane_value(sy_l, s), sz = lane_value(sz_l, s);
+        const int cx0 = __builtin_amdgcn_readlane(cx0_l, s), cx1 = __builtin_amdgcn_readlane(cx1_l, s);
+        const int cy0 = __builtin_amdgcn_readlane(cy0_l, s), cy1 = __builtin_amdgcn_readlane(cy1_l, s);
+        const float slx = lo.x + sx, shx = hi.x + sx, sly = lo.y + sy, shy = hi.y + sy, slz = lo.z + sz,
+                    shz = hi.z + sz;
+        const float px = pi.x + sx, py = pi.y + sy, pz = pi.z + sz;   // lane k: shifted i-particle k
+        const int kmin = s == 13 ? (ci * M + 1) / N : 0;   // half list: the first cj with cj * N + N - 1 > ci * M
+        const int ncy = cy1 - cy0 + 1, ncols = (cx1 - cx0 + 1) * ncy;
+        const float rncy = __builtin_amdgcn_rcpf((float)ncy);
+        const int c_lo = ncols * part / P, c_hi = ncols * (part + 1) / P;   // this part's columns
+        for (int cb = c_lo; cb < c_hi; cb += 64) {
+            // one column per lane (ascending column id): its z window of j-clusters
+            int k0 = 0, kc = 0;
+            const int cidx = cb + lane;
+            if (cidx < c_hi) {
+                const int row = (int)(((float)cidx + 0.5f) * rncy);   // cidx / ncy (exact: cidx is below 2^20)
+                const int c = (cx0 + row) * a.ny + cy0 + cidx - row * ncy;
+                const float4 cbb = ld(a.colbb + c);
+                const float gx = axis_gap(cbb.x, cbb.z, slx, shx), gy = axis_gap(cbb.y, cbb.w, sly, shy);
+                const float g2 = gx * gx + gy * gy;
+                if (g2 < a.rl2) {
+                    // a j-cluster in this column lies at least (gx, gy) away in x and y, so
+                    // only z gaps below sqrt(rlist^2 - g^2) can pass the box test
+                    const float zr = sqrtf(a.rl2 - g2) + zmargin;
+                    const int j0 = max(a.col_start[c] / N, kmin), j1 = a.col_start[c + 1] / N;
+                    // a j-cluster of padding only (a column's last one when N is below the
+                    // column granule) has an empty box, hi = -inf: it sorts as +inf, keeping
+                    // the key nondecreasing
+                    k0 = lower_bound(j0, j1, [&](int k) {
+                        const float4 h = ld(a.bbj_hi + k);
+                        return h.x == -INFINITY ? INFINITY : h.z;
+                    }, slz - zr);
+                    const int k1 = lower_bound(k0, j1, [&](int k) { return ld(a.bbj_lo + k).z; }, shz + zr);
+                    kc = max(0, k1 - k0);
+                }
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const int ncy = cy1 - cy0 + 1, ncols = (cx1 - cx0 + 1) * ncy;
-            const int c_lo = ncols * part / P, c_hi = ncols * (part + 1) / P;   // this part's columns
-            for (int cb = c_lo; cb < c_hi; cb += 64) {
-                // one column per lane (ascending column id): its z window of j-clusters
-                int k0 = 0, kc = 0;
-                const int cidx = cb + lane;
-                if (cidx < c_hi) {
-                    const int c = (cx0 + cidx / ncy) * a.ny + cy0 + cidx % ncy;
-                    const float4 cbb = ld(a.colbb + c);
-                    const float gx = axis_gap(cbb.x, cbb.z, slx, shx), gy = axis_gap(cbb.y, cbb.w, sly, shy);
-                    const float g2 = gx * gx + gy * gy;
-                    if (g2 < a.rl2) {
-                        // a j-cluster in this column lies at least (gx, gy) away in x and y, so
-                        // only z gaps below sqrt(rlist^2 - g^2) can pass the box test
-                        const float zr = sqrtf(a.rl2 - g2) + zmargin;
-                        const int j0 = a.col_start[c] / N, j1 = a.col_start[c + 1] / N;
-                        // a j-cluster of padding only (a column's last one when N is below the
-                        // column granule) has an empty box, hi = -inf: it sorts as +inf, keeping
-                        // the key nondecreasing
-                        k0 = lower_bound(j0, j1, [&](int k) {
-                            const float4 h = ld(a.bbj_hi + k);
-                            return h.x == -INFINITY ? INFINITY : h.z;
-                        }, slz - zr);
-                        const int k1 = lower_bound(k0, j1, [&](int k) { return ld(a.bbj_lo + k).z; }, shz + zr);
-                        kc = k1 - k0;
-                    }
+            // flatten the windows of the 64 columns: exclusive offsets by a wave scan
+            const int incl = lane_scan(kc);
+            const int total = __builtin_amdgcn_readlane(incl, 63);
+            const int excl = incl - kc;
+            // lane q: the flattened index of its partner's j-cluster, -1 unless the pair is within rlist in this image
+            int xt = -1;
+            if (FILL && staged && nexcl > 0) {
+                const int pc = (xcol_x - cx0) * ncy + xcol_y - cy0 - cb;
+                const int from = pc & 63, off = (xv >> 3) / N - __shfl(k0, from, 64), len = __shfl(kc, from, 64);
+                const bool here = lane < nexcl && xcol_x >= cx0 && xcol_y >= cy0 && xcol_y <= cy1 && pc >= 0 &&
+                                  pc < min(64, c_hi - cb) && off >= 0 && off < len;
+                const int at = __shfl(excl, from, 64) + off, ia = xv & 7;
+                const float d2 = sq3(__shfl(px, ia, 64) - xp.x, __shfl(py, ia, 64) - xp.y, __shfl(pz, ia, 64) - xp.z);
+                if (here && d2 < a.rl2) xt = at;
+            }
+            for (int t0 = 0; t0 < total; t0 += 64) {
+                const int t = t0 + lane;
+                // owner column: the last lane whose exclusive offset is <= t (fixed six-step search,
+                // executed by every lane so that all shuffles read active lanes)
+                const int tt = t < total ? t : total - 1;
+                int own = 0;
+#pragma unroll
+                for (int step = 32; step > 0; step >>= 1) {
+                    const int ev = __shfl(excl, own + step, 64);   // own + step <= 63
+                    if (ev <= tt) own += step;
                 }
-                // flatten the windows of the 64 columns: exclusive offsets by a wave scan
-                int incl = kc;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int v = __shfl_up(incl, o, 64);
-                    if (lane >= o) incl += v;
+                const int cj = __shfl(k0, own, 64) + (tt - __shfl(excl, own, 64));
+                bool acc = false, need = false;
+                float d2 = 0.0f;
+                int nj = 0;   // the candidate's real slots: the first nj (its box's lo.w holds their mask)
+                if (t < total) {
+                    const float4 jl = ld(a.bbj_lo + cj), jh = ld(a.bbj_hi + cj);
+                    d2 = sq3(axis_gap(jl.x, jh.x, slx, shx), axis_gap(jl.y, jh.y, sly, shy),
+                             axis_gap(jl.z, jh.z, slz, shz));
+                    nj = __popc(__float_as_uint(jl.w));
+                    acc = d2 < a.rl2;
+                    need = acc && !(d2 < a.rb2);
                 }
-                const int total = __shfl(incl, 63, 64);
-                const int excl = incl - kc;
-                for (int t0 = 0; t0 < total; t0 += 64) {
-                    const int t = t0 + lane;
-                    bool ok = t < total;
-                    // owner column: the last lane whose exclusive offset is <= t (fixed six-step search,
-                    // executed by every lane so that all shuffles read active lanes)
-                    const int tt = ok ? t : total - 1;
-                    int own = 0;
+                const unsigned long long nm = __ballot(need);
+                if (nm) {
+                    const int r = __popcll(nm & below), nq = __popcll(nm);
+                    if (need) queue[w][r] = ((unsigned)cj << 4) | (unsigned)nj;
+                    lds_fence();
+                    float qx[M], qy[M], qz[M];
 #pragma unroll
-                    for (int step = 32; step > 0; step >>= 1) {
-                        const int cand = own + step;
-                        const int ev = __shfl(excl, cand < 64 ? cand : 63, 64);
-                        if (cand < 64 && ev <= tt) own = cand;
+                    for (int k = 0; k < M; ++k) {
+                        qx[k] = lane_value(px, k);
+                        qy[k] = lane_value(py, k);
+                        qz[k] = lane_value(pz, k);
                     }
-                    const int cj = __shfl(k0, own, 64) + (tt - __shfl(excl, own, 64));
-                    if (ok && s == 13) ok = cj * N + N - 1 > ci * M;
-                    float d2 = 0.0f;
-                    unsigned jreal = 0;   // the candidate's real slots (its box's lo.w)
-                    if (ok) {
-                        const float4 jl = ld(a.bbj_lo + cj), jh = ld(a.bbj_hi + cj);
-                        d2 = sq3(axis_gap(jl.x, jh.x, slx, shx), axis_gap(jl.y, jh.y, sly, shy),
-                                 axis_gap(jl.z, jh.z, slz, shz));
-                        ok = d2 < a.rl2;
-                        jreal = __float_as_uint(jl.w);
+                    const int b = lane % N, g = lane / N;
+                    for (int q0 = 0; q0 < nq; q0 += G) {
+                        const unsigned cq = queue[w][min(q0 + g, nq - 1)];
+                        const float4 pj = ld(a.xs + (int)(cq >> 4) * N + b);
+                        bool near = false;
+#pragma unroll
+                        for (int k = 0; k < M; ++k) near |= sq3(qx[k] - pj.x, qy[k] - pj.y, qz[k] - pj.z) < a.rl2;
+                        const unsigned long long hb = __ballot(near && b < (int)(cq & 15u));
+                        if (need && r >= q0 && r < q0 + G)
+                            acc = (hb >> ((r - q0) * N)) & ((1ull << N) - 1ull);
                     }
-                    bool acc = ok;
-                    if (ok && !(d2 < a.rb2)) {
-                        // particle-pair check of this lane's candidate, four j-particles per step
-                        // with their loads in flight together (early exit between steps)
-                        bool hit = false;
-                        for (int b0 = 0; b0 < N && !hit; b0 += 4) {
-                            float4 pj[4];
+                    lds_fence();   // the next batch's queue
+                }
+                const unsigned long long accepted = __ballot(acc);
+                if (FILL && accepted) {
+                    // mask bit b*M + a: both particles real, slot(i) < slot(j) for the unshifted
+                    // self/overlapping pair, not an exclusion in this image
+                    constexpr unsigned long long kEach = M == 8 ? 0x0101010101010101ull : 0x1111111111111111ull;
+                    unsigned long long mask = (nj * M == 64 ? ~0ull : (1ull << (nj * M)) - 1ull) & (ireal * kEach);
+                    if (s == 13 && cj * N < ci * M + M) {
 #pragma unroll
-                            for (int u = 0; u < 4; ++u) pj[u] = ld(a.xs + cj * N + b0 + u);
-                            bool near[4];
-#pragma unroll
-                            for (int u = 0; u < 4; ++u) {   // real and near the whole i-cluster's box
-                                const float g = sq3(axis_gap(pj[u].x, pj[u].x, slx, shx),
-                                                    axis_gap(pj[u].y, pj[u].y, sly, shy),
-                                                    axis_gap(pj[u].z, pj[u].z, slz, shz));
-                                near[u] = ((jreal >> (b0 + u)) & 1u) && g < rp2;
-                            }
-#pragma unroll
-                            for (int ia = 0; ia < M; ++ia) {
-                                if (!((ireal >> ia) & 1u)) continue;
-                                const float4 pi = ipos[w][ia];
-#pragma unroll
-                                for (int u = 0; u < 4; ++u)
-                                    hit |= near[u] && sq3(pi.x - pj[u].x, pi.y - pj[u].y, pi.z - pj[u].z) < a.rl2;
-                            }
+                        for (int b = 0; b < N; ++b) {
+                            const int tr = cj * N + b - ci * M;
+                            const unsigned drop = FULL & ~(tr >= M ? FULL : (tr <= 0 ? 0u : (1u << tr) - 1u));
+                            mask &= ~((unsigned long long)drop << (b * M));
                         }
-                        acc = hit;
                     }
-                    const unsigned long long accepted = __ballot(acc);
-                    if (FILL) {
-                        if (acc) {
-                            // mask bit b*M + a: both particles real, slot(i) < slot(j) for the unshifted
-                            // self/overlapping pair, not an exclusion in this image
-                            unsigned long long mask = 0;
-#pragma unroll
-                            for (int b = 0; b < N; ++b) {
-                                const int sb = cj * N + b;
-                                unsigned keep = ((jreal >> b) & 1u) ? ireal : 0u;
-                                if (s == 13) {
-                                    const int tr = sb - ci * M;
-                                    keep &= tr >= M ? FULL : (tr <= 0 ? 0u : (1u << tr) - 1u);
-                                }
-                                mask |= (unsigned long long)keep << (b * M);
-                            }
-                            if (staged) {
-                                // only a j-cluster holding a staged partner's slot can lose mask bits
-                                // partner q's slot and i-index are read from lane q's register: no
-                                // memory wait unless the partner lies in this lane's candidate
-                                if (cj * N + N - 1 >= xlo && cj * N <= xhi) {
-                                    for (int q = 0; q < nexcl; ++q) {
-                                        const int v = __builtin_amdgcn_readlane(xv, q), ia = v & 7,
-                                                  b = (v >> 3) - cj * N;
-                                        if (b < 0 || b >= N) continue;
-                                        const float4 pj = xpos[w][q], pi = ipos[w][ia];
-                                        if (sq3(pi.x - pj.x, pi.y - pj.y, pi.z - pj.z) < a.rl2)
-                                            mask &= ~(1ull << (b * M + ia));
-                                    }
-                                }
-                            } else {   // more partners than staged: read them from the CSR arrays
-                                for (int ia = 0; ia < M; ++ia) {
-                                    if (!((ireal >> ia) & 1u)) continue;
-                                    const int io = a.perm[ci * M + ia];
-                                    for (int e = a.excl_off[io]; e < a.excl_off[io + 1]; ++e) {
-                                        const int ps = a.slot_of[a.excl_idx[e]];
-                                        const int b = ps - cj * N;
-                                        if (b < 0 || b >= N) continue;
-                                        const float4 pj = ld(a.xs + ps), pi = ipos[w][ia];
-                                        if (sq3(pi.x - pj.x, pi.y - pj.y, pi.z - pj.z) < a.rl2)
-                                            mask &= ~(1ull << (b * M + ia));
-                                    }
-                                }
-                            }
-                            const int rank = cnt + __popcll(accepted & ((1ull << lane) - 1ull));
-                            if (rank < resv) {
-                                nb_jentry en;
-                                en.cj = cj;
-                                en.shift = s;
-                                en.mlo = (uint32_t)mask;
-                                en.mhi = (uint32_t)(mask >> 32);
-                                st(a.entries + wpos + rank, en);
-                                if (a.keys) a.keys[wpos + rank] = d2;
-                                a.jrank[wpos + rank] = atomicAdd((int *)a.jcount + cj, 1);
+                    if (staged) {
+                        const int xl = xt - t0;
+                        const bool hits = xt >= 0 && xl >= 0 && xl < 64;
+                        if (__ballot(hits)) {
+                            mexcl[w][lane] = mask;
+                            lds_fence();
+                            const int ps = xv >> 3;
+                            if (hits) atomicAnd(&mexcl[w][xl], ~(1ull << ((ps & (N - 1)) * M + (xv & 7))));
+                            lds_fence();
+                            mask = mexcl[w][lane];
+                            lds_fence();
+                        }
+                    } else if (acc) {   // more partners than lanes: read them from the CSR arrays
+                        for (int ia = 0; ia < M; ++ia) {
+                            if (!((ireal >> ia) & 1u)) continue;
+                            const int io = a.perm[ci * M + ia];
+                            const float4 p = ld(a.xs + ci * M + ia);
+                            for (int e = a.excl_off[io]; e < a.excl_off[io + 1]; ++e) {
+                                const int ps = a.slot_of[a.excl_idx[e]];
+                                const int b = ps - cj * N;
+                                if (b < 0 || b >= N) continue;
+                                const float4 pj = ld(a.xs + ps);
+                                if (sq3(p.x + sx - pj.x, p.y + sy - pj.y, p.z + sz - pj.z) < a.rl2)
+                                    mask &= ~(1ull << (b * M + ia));
                             }
                         }
                     }
-                    cnt += __popcll(accepted);
+                    const int rank = cnt + __popcll(accepted & below);
+                    if (acc && rank < resv) {
+                        nb_jentry en;
+                        en.cj = cj;
+                        en.shift = s;
+                        en.mlo = (uint32_t)mask;
+                        en.mhi = (uint32_t)(mask >> 32);
+                        st(a.entries + wpos + rank, en);
+                        if (a.keys) a.keys[wpos + rank] = d2;
+                        a.jrank[wpos + rank] = atomicAdd((int *)a.jcount + cj, 1);
+                    }
                 }
+                cnt += __popcll(accepted);
             }
         }
     }
