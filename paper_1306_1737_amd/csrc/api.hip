@@ -230,7 +230,7 @@ int nb_sync(nb_ctx *c) {
 static void grid_release(nb_grid *g) {
     DevBuf *bufs[] = {&g->col_count, &g->col_start, &g->col_fill, &g->colbb, &g->col_hist, &g->atom_col, &g->atom_xw,
                       &g->atom_img, &g->bucket, &g->xs, &g->xs_now, &g->type_s, &g->perm, &g->img_s,
-                      &g->slot_of, &g->bbi_lo, &g->bbi_hi, &g->bbj_lo, &g->bbj_hi, &g->nslots,
+                      &g->slot_of, &g->bbi_lo, &g->bbi_hi, &g->bbj_lo, &g->bbj_hi, &g->zfirst, &g->nslots,
                       &g->shiftvec};
     for (DevBuf *b : bufs) release(*b);
 }
@@ -275,6 +275,10 @@ int nb_grid_sort(nb_ctx *c, const double box[3], int n, const float *xyzq, const
     g->inv_x = (float)((double)g->nx / box[0]);
     g->inv_y = (float)((double)g->ny / box[1]);
     g->ncol = g->nx * g->ny;
+    // four z bins per column spacing, about four per j-cluster: a window looked up in them holds an eighth of a
+    // cluster more at either end than the exact one
+    g->nz = (int)std::fmin(std::fmax(std::floor(4.0 * box[2] / s), 1.0), 65536.0);
+    g->inv_z = (float)((double)g->nz / box[2]);
     long cap = (long)n + (long)g->ncol * (g->cmax - 1);
     cap = (cap + g->cmax - 1) / g->cmax * g->cmax;
     if (cap > (1L << 30)) return fail(NB_ERR_ARG, "nb_grid_sort: too many particles");
@@ -302,6 +306,7 @@ int nb_grid_sort(nb_ctx *c, const double box[3], int n, const float *xyzq, const
         rc = rc ? rc : ensure(g->ctx, g->bbj_lo, ns / g->nn * 16);
         rc = rc ? rc : ensure(g->ctx, g->bbj_hi, ns / g->nn * 16);
     }
+    rc = rc ? rc : ensure(g->ctx, g->zfirst, nc * (size_t)g->nz * 8);
     rc = rc ? rc : ensure(g->ctx, g->nslots, 16);
     rc = rc ? rc : ensure(g->ctx, g->shiftvec, 32 * 16);
     if (rc == NB_OK) {

@@ -158,6 +158,9 @@ struct SortArgs {
     int *flags;
     int m, nn;                                   // i- and j-cluster sizes
     float4 *bbi_lo, *bbi_hi, *bbj_lo, *bbj_hi;   // cluster bounding boxes
+    int2 *zfirst;                                // z index of the columns' j-clusters (z_index)
+    int nz;
+    float inv_z;
 };
 
 // Bounding box of each cluster of `size` slots among clusters [c0, c1), one thread per cluster
@@ -180,6 +183,28 @@ __device__ inline void cluster_boxes(const float4 *xs, const int *perm, int size
         l.w = __uint_as_float(real);
         lo[cl] = l;
         hi[cl] = h;
+    }
+}
+
+// z index of a column's j-clusters [j0, j1), which the pair search reads instead of searching their boxes: for
+// every z bin b, x = the first cluster whose hi.z lies in bin b or above, y = the first whose lo.z lies above
+// bin b (j1 if none).  Clusters of padding only (the last ones) lie above every bin.
+__device__ inline void z_index(const SortArgs &a, int c, const float4 *lo, const float4 *hi, int j0, int j1, int t,
+                               int nt) {
+    int2 *row = a.zfirst + (long)c * a.nz;
+    auto top = [&](int k) {   // bin of hi.z
+        if (k >= j1 || hi[k].x == -INFINITY) return a.nz;
+        return mxn::z_bin(hi[k].z, a.inv_z, a.nz);
+    };
+    auto bottom = [&](int k) {   // bin of lo.z
+        if (k >= j1 || hi[k].x == -INFINITY) return a.nz;
+        return mxn::z_bin(lo[k].z, a.inv_z, a.nz);
+    };
+    // cluster k is the first for the bins above its predecessor's and up to its own; k = j1 closes the row
+    for (int k = j0 + t; k <= j1; k += nt) {
+        const int t1 = min(top(k), a.nz - 1), b1 = min(bottom(k) - 1, a.nz - 1);
+        for (int b = k > j0 ? top(k - 1) + 1 : 0; b <= t1; ++b) row[b].x = k;
+        for (int b = k > j0 ? bottom(k - 1) : 0; b <= b1; ++b) row[b].y = k;
     }
 }
 
@@ -266,6 +291,9 @@ __device__ inline void col_sort_body(const SortArgs &a, int c) {
     // the slots written above are visible to the workgroup after the reduction's barriers
     cluster_boxes(a.xs, a.perm, a.m, start / a.m, end / a.m, a.bbi_lo, a.bbi_hi, tid, kSortThreads);
     if (a.nn != a.m) cluster_boxes(a.xs, a.perm, a.nn, start / a.nn, end / a.nn, a.bbj_lo, a.bbj_hi, tid, kSortThreads);
+    __syncthreads();
+    z_index(a, c, a.nn != a.m ? a.bbj_lo : a.bbi_lo, a.nn != a.m ? a.bbj_hi : a.bbi_hi, start / a.nn, end / a.nn, tid,
+            kSortThreads);
 }
 
 __global__ __launch_bounds__(kSortThreads) void k_col_sort(SortArgs a) { col_sort_body(a, blockIdx.x); }
@@ -369,7 +397,7 @@ static SortArgs make_sort(const nb_grid *g, const int *type) {
                     (const int *)g->atom_img.p, (const float4 *)g->atom_xw.p, (float4 *)g->xs.p, (float4 *)g->xs_now.p,
                     (float4 *)g->colbb.p, (int *)g->type_s.p, (int *)g->perm.p, (int *)g->img_s.p,
                     (int *)g->slot_of.p, g->ctx->d_flags, g->m, g->nn, (float4 *)g->bbi_lo.p, (float4 *)g->bbi_hi.p,
-                    (float4 *)g->bbj_lo.p, (float4 *)g->bbj_hi.p};
+                    (float4 *)g->bbj_lo.p, (float4 *)g->bbj_hi.p, (int2 *)g->zfirst.p, g->nz, g->inv_z};
 }
 
 size_t grid_job_size() { return sizeof(GridJob); }

@@ -128,13 +128,15 @@ struct nb_grid {
     double box[3] = {0, 0, 0};
     float Lf[3] = {0, 0, 0};
     double invL[3] = {0, 0, 0};
-    float inv_x = 0, inv_y = 0;
+    float inv_x = 0, inv_y = 0, inv_z = 0;   // columns per length in x and y, z bins per length
+    int nz = 0;                 // z bins of a column's cluster index (zfirst)
     double spacing = 0;
     // device storage
     mxn::DevBuf col_count, col_start, col_fill, colbb, col_hist;
     mxn::DevBuf atom_col, atom_xw, atom_img, bucket;
     mxn::DevBuf xs, xs_now, type_s, perm, img_s, slot_of;
     mxn::DevBuf bbi_lo, bbi_hi, bbj_lo, bbj_hi;
+    mxn::DevBuf zfirst;        // int2 per (column, z bin): see z_index in grid.hip
     mxn::DevBuf nslots;        // int on device
     mxn::DevBuf shiftvec;      // 27 float4 image shift vectors
     long generation = 0;       // incremented by every sort; lists remember the one they were built on
@@ -220,6 +222,12 @@ struct nb_mlp {
 };
 
 namespace mxn {
+
+// z bin of a coordinate in a column's cluster index; nondecreasing in z
+__host__ __device__ inline int z_bin(float z, float inv_z, int nz) {
+    const float b = floorf(z * inv_z);
+    return b > 0.0f ? (b < (float)nz ? (int)b : nz - 1) : 0;
+}
 
 constexpr int kMlpParams = 4801;
 int launch_batch(nb_ctx *ctx, nb_batch *b, const nb_params *p, unsigned flags, double *energy, double *virial);

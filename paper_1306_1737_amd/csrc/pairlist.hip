@@ -32,9 +32,10 @@ struct SearchArgsT {
     P<const int> perm, slot_of;
     P<const float4> bbi_lo, bbi_hi, bbj_lo, bbj_hi, colbb;
     P<const int> col_start;
+    P<const int> zfirst;                 // (x, y) per (column, z bin), see z_index in grid.hip
     P<const int> excl_off, excl_idx;
-    float Lx, Ly, Lz, inv_x, inv_y;
-    int nx, ny;
+    float Lx, Ly, Lz, inv_x, inv_y, inv_z;
+    int nx, ny, nz;
     float rlist, rl2, rb2;
     P<int> part_count;                   // entries found by each (i-cluster, part)
     P<const int> part_start;             // region of each (i-cluster, part)
@@ -60,10 +61,11 @@ __device__ inline SearchArgsG to_global(const SearchArgs &a) {
     g.bbj_hi = (gptr<const float4>)a.bbj_hi;
     g.colbb = (gptr<const float4>)a.colbb;
     g.col_start = (gptr<const int>)a.col_start;
+    g.zfirst = (gptr<const int>)a.zfirst;
     g.excl_off = (gptr<const int>)a.excl_off;
     g.excl_idx = (gptr<const int>)a.excl_idx;
-    g.Lx = a.Lx; g.Ly = a.Ly; g.Lz = a.Lz; g.inv_x = a.inv_x; g.inv_y = a.inv_y;
-    g.nx = a.nx; g.ny = a.ny;
+    g.Lx = a.Lx; g.Ly = a.Ly; g.Lz = a.Lz; g.inv_x = a.inv_x; g.inv_y = a.inv_y; g.inv_z = a.inv_z;
+    g.nx = a.nx; g.ny = a.ny; g.nz = a.nz;
     g.rlist = a.rlist; g.rl2 = a.rl2; g.rb2 = a.rb2;
     g.part_count = (gptr<int>)a.part_count;
     g.part_start = (gptr<const int>)a.part_start;
@@ -82,17 +84,6 @@ __device__ inline float axis_gap(float jlo, float jhi, float ilo, float ihi) {
     float d1 = jlo - ihi, d2 = ilo - jhi;
     float m = d1 > d2 ? d1 : d2;
     return m > 0.0f ? m : 0.0f;
-}
-
-// first index k in [lo, hi) with key(k) >= v for a nondecreasing key (hi if none)
-template <class F>
-__device__ inline int lower_bound(int lo, int hi, F key, float v) {
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (key(mid) < v) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
 }
 
 // inclusive sum over the lanes at and below this one (DPP row shifts, then row broadcasts)
@@ -123,8 +114,9 @@ __device__ inline void lds_fence() {
 //     have any are walked (one, for a cluster away from the faces).  For the
 //     zero shift columns before the i-cluster's own hold nothing of the half
 //     list and are left out, and so are earlier clusters of a window.
-//   - Lanes own candidate columns (binary search of the z window), then, after
-//     a scan flattens the windows, candidate j-clusters (box test).
+//   - Lanes own candidate columns (the z window looked up in the grid's z
+//     index, one load in place of two binary searches of about ten in a row),
+//     then, after a scan flattens the windows, candidate j-clusters (box test).
 //   - The particle check of the candidates outside the rBB shortcut is taken
 //     by all lanes together: the candidates are queued in LDS and 64/N of them
 //     are checked at a time, lane = (candidate, j-particle), the M i-particles
@@ -240,15 +232,10 @@ __device__ inline void search_body(const A &a, int blk) {
                     // a j-cluster in this column lies at least (gx, gy) away in x and y, so
                     // only z gaps below sqrt(rlist^2 - g^2) can pass the box test
                     const float zr = sqrtf(a.rl2 - g2) + zmargin;
-                    const int j0 = max(a.col_start[c] / N, kmin), j1 = a.col_start[c + 1] / N;
-                    // a j-cluster of padding only (a column's last one when N is below the
-                    // column granule) has an empty box, hi = -inf: it sorts as +inf, keeping
-                    // the key nondecreasing
-                    k0 = lower_bound(j0, j1, [&](int k) {
-                        const float4 h = ld(a.bbj_hi + k);
-                        return h.x == -INFINITY ? INFINITY : h.z;
-                    }, slz - zr);
-                    const int k1 = lower_bound(k0, j1, [&](int k) { return ld(a.bbj_lo + k).z; }, shz + zr);
+                    const int z0 = (c * a.nz + mxn::z_bin(slz - zr, a.inv_z, a.nz)) * 2;
+                    const int z1 = (c * a.nz + mxn::z_bin(shz + zr, a.inv_z, a.nz)) * 2;
+                    k0 = max((int)a.zfirst[z0], kmin);
+                    const int k1 = a.zfirst[z1 + 1];
                     kc = max(0, k1 - k0);
                 }
             }
@@ -852,11 +839,12 @@ static SearchArgs make_search(const nb_list *l, const int *excl_off, const int *
     a.bbj_hi = (const float4 *)(g->nn == g->m ? g->bbi_hi.p : g->bbj_hi.p);
     a.colbb = (const float4 *)g->colbb.p;
     a.col_start = (const int *)g->col_start.p;
+    a.zfirst = (const int *)g->zfirst.p;
     a.excl_off = excl_off;
     a.excl_idx = excl_idx;
     a.Lx = g->Lf[0]; a.Ly = g->Lf[1]; a.Lz = g->Lf[2];
-    a.inv_x = g->inv_x; a.inv_y = g->inv_y;
-    a.nx = g->nx; a.ny = g->ny;
+    a.inv_x = g->inv_x; a.inv_y = g->inv_y; a.inv_z = g->inv_z;
+    a.nx = g->nx; a.ny = g->ny; a.nz = g->nz;
     a.rlist = l->rlist;
     volatile float rl2 = l->rlist * l->rlist, rb2 = l->rbb * l->rbb;
     a.rl2 = rl2; a.rb2 = rb2;
