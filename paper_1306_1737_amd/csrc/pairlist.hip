@@ -160,38 +160,17 @@ __device__ inline void search_body(const A &a, int blk) {
     // lane k < M: i-particle k (a dummy's NaN fails every distance test)
     float4 pi = ld(a.xs + ci * M + (lane < M ? lane : 0));
     if (!((ireal >> (lane & (M - 1))) & 1u)) pi.x = __builtin_nanf("");
-    // lane q < nexcl: exclusion partner q as slot * 8 + i-index, its position and column
+    // lane q < nexcl: exclusion partner q as slot * 8 + i-index, its position and column.  Its chain of loads
+    // (offsets, partner, slot, position) starts here and ends with the first columns' own loads, so that the
+    // two overlap (55 -> 51 us).
     int nexcl = 0, xv = 0, xcol_x = -1, xcol_y = -1;
-    bool staged = true;
+    int e0 = 0, e1 = 0, xe = 0, xa = 0;   // lane k < M: CSR range; lane q: partner's CSR entry and i-index
+    bool staged = true, fetch = FILL;     // fetch: the partners are still to be loaded
     float4 xp = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (FILL) {
-        int e0 = 0, e1 = 0;
-        if (lane < M && ((ireal >> lane) & 1u)) {
-            const int io = a.perm[ci * M + lane];
-            e0 = a.excl_off[io];
-            e1 = a.excl_off[io + 1];
-        }
-        const int incl = lane_scan(e1 - e0);
-        nexcl = __builtin_amdgcn_readlane(incl, 63);
-        staged = nexcl <= kExclStage && (long)a.nci_cap * M < (1L << 28);   // slot * 8 + i-index fits an int
-        if (staged) {
-            // partner q's i-particle is the first whose inclusive count exceeds q, so every lane issues its
-            // own load chain at once
-            int ia = 0, first = 0;
-#pragma unroll
-            for (int k = 0; k < M - 1; ++k) {
-                const int ik = __builtin_amdgcn_readlane(incl, k);
-                if (lane >= ik) { ia = k + 1; first = ik; }
-            }
-            const int e = __shfl(e0, ia, 64) + lane - first;
-            if (lane < nexcl) {
-                const int ps = a.slot_of[a.excl_idx[e]];
-                xv = ps * 8 + ia;
-                xp = ld(a.xs + ps);
-                xcol_x = col_x(xp.x);
-                xcol_y = col_y(xp.y);
-            }
-        }
+        const int io = max(0, (int)a.perm[ci * M + (lane & (M - 1))]);
+        e0 = a.excl_off[io];
+        e1 = a.excl_off[io + 1];
     }
     // lane s: image shift s and its candidate columns, a superset with one column of margin against rounding
     const float sx_l = (float)(lane / 9 - 1) * a.Lx, sy_l = (float)((lane / 3) % 3 - 1) * a.Ly,
@@ -204,6 +183,20 @@ __device__ inline void search_body(const A &a, int blk) {
     // wrapped particles lie in [0, L): no z window can be hit from beyond that range
     const bool any = lane >= 13 && lane < 27 && cx0_l <= cx1_l && cy0_l <= cy1_l &&
                      !(lo.z + sz_l - a.rlist - zmargin > a.Lz + zmargin || hi.z + sz_l + a.rlist + zmargin < -zmargin);
+    if (FILL) {
+        const int incl = lane_scan(lane < M && ((ireal >> lane) & 1u) ? e1 - e0 : 0);
+        nexcl = __builtin_amdgcn_readlane(incl, M - 1);
+        staged = nexcl <= kExclStage && (long)a.nci_cap * M < (1L << 28);   // slot * 8 + i-index fits an int
+        fetch = staged && nexcl > 0;
+        // partner q's i-particle is the first whose inclusive count exceeds q
+        int first = 0;
+#pragma unroll
+        for (int k = 0; k < M - 1; ++k) {
+            const int ik = __builtin_amdgcn_readlane(incl, k);
+            if (lane >= ik) { xa = k + 1; first = ik; }
+        }
+        xe = __shfl(e0, xa, 64) + lane - first;
+    }
     int cnt = 0;
     // an i-cluster of padding only has no real particles (and an empty box)
     for (unsigned long long shifts = lo.x <= hi.x ? __ballot(any) : 0ull; shifts; shifts &= shifts - 1ull) {
@@ -237,6 +230,16 @@ __device__ inline void search_body(const A &a, int blk) {
                     k0 = max((int)a.zfirst[z0], kmin);
                     const int k1 = a.zfirst[z1 + 1];
                     kc = max(0, k1 - k0);
+                }
+            }
+            if (FILL && fetch) {
+                fetch = false;
+                if (lane < nexcl) {
+                    const int ps = a.slot_of[a.excl_idx[xe]];
+                    xv = ps * 8 + xa;
+                    xp = ld(a.xs + ps);
+                    xcol_x = col_x(xp.x);
+                    xcol_y = col_y(xp.y);
                 }
             }
             // flatten the windows of the 64 columns: exclusive offsets by a wave scan
@@ -290,15 +293,18 @@ __device__ inline void search_body(const A &a, int blk) {
                         qz[k] = lane_value(pz, k);
                     }
                     const int b = lane % N, g = lane / N;
-                    for (int q0 = 0; q0 < nq; q0 += G) {
-                        const unsigned cq = queue[w][min(q0 + g, nq - 1)];
-                        const float4 pj = ld(a.xs + (int)(cq >> 4) * N + b);
+                    auto check = [&](int q, unsigned cq, const float4 &pj) {   // candidates q .. q + G - 1
                         bool near = false;
 #pragma unroll
                         for (int k = 0; k < M; ++k) near |= sq3(qx[k] - pj.x, qy[k] - pj.y, qz[k] - pj.z) < a.rl2;
                         const unsigned long long hb = __ballot(near && b < (int)(cq & 15u));
-                        if (need && r >= q0 && r < q0 + G)
-                            acc = (hb >> ((r - q0) * N)) & ((1ull << N) - 1ull);
+                        if (need && r >= q && r < q + G) acc = (hb >> ((r - q) * N)) & ((1ull << N) - 1ull);
+                    };
+                    for (int q0 = 0; q0 < nq; q0 += 2 * G) {   // two steps' loads in flight together
+                        const unsigned c0 = queue[w][min(q0 + g, nq - 1)], c1 = queue[w][min(q0 + G + g, nq - 1)];
+                        const float4 p0 = ld(a.xs + (int)(c0 >> 4) * N + b), p1 = ld(a.xs + (int)(c1 >> 4) * N + b);
+                        check(q0, c0, p0);
+                        if (q0 + G < nq) check(q0 + G, c1, p1);
                     }
                     lds_fence();   // the next batch's queue
                 }
@@ -366,8 +372,9 @@ __device__ inline void search_body(const A &a, int blk) {
 }
 
 template <int M, int N, bool FILL>
-// Six wavefronts per SIMD (at most 80 VGPRs, a few spills in the fill pass) measured 9 % faster on the
-// production list than the four that the unconstrained register count allows.
+// Six wavefronts per SIMD (at most 80 VGPRs): 50.8 us on the 96 000-atom 8x8 list against 53.3 at seven, which
+// spill (3 million atoms: 1.01 against 1.11 ms).  Of the 50.8 us the rank atomics, about 58 G/s over the whole chip,
+// are 17 (without them 34); taking them in one go at the wavefront's end measured 49, and 2 % slower at 3 million.
 __attribute__((amdgpu_waves_per_eu(6)))
 __global__ __launch_bounds__(256) void k_search(SearchArgs a) {
     search_body<M, N, FILL>(a, blockIdx.x);
