@@ -67,6 +67,7 @@ struct ForceArgs {
     double *blockpart;   // energy reduction: per-share sums [kNAcc][kReduceParts]
     double *energy, *virial;
     int ener, vir;
+    int shares;        // workgroups that total one quantity (FP64 sums)
     int parts;         // regions per i-cluster
     int sci;           // i-clusters per work-item group of the fold's i-forces (super-cluster kernel), else 1
     int n;
@@ -135,6 +136,24 @@ __device__ inline float wave_sum_dpp(float v) {
     x = __float_as_int(__int_as_float(x) + __int_as_float(__builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false)));
     return __int_as_float(x);
 }
+
+// The same for FP64 (and FP32) sums of a work item; total in lane 63.
+template <int CTRL, int ROWS>
+__device__ inline double dpp_move(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, ROWS == 0xf);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, ROWS == 0xf);
+    return __hiloint2double(hi, lo);
+}
+__device__ inline double item_sum(double v) {
+    v += dpp_move<0x111, 0xf>(v);
+    v += dpp_move<0x112, 0xf>(v);
+    v += dpp_move<0x114, 0xf>(v);
+    v += dpp_move<0x118, 0xf>(v);
+    v += dpp_move<0x142, 0xa>(v);
+    v += dpp_move<0x143, 0xc>(v);
+    return v;
+}
+__device__ inline float item_sum(float v) { return wave_sum_dpp(v); }
 
 // Per-type-pair table in LDS: row 1 + ti*nt + tj = (6 C6, 12 C12, 12 x LJ
 // shift at rc, Coulomb shift at rc), and the all-zero row 0 that a pair with a
@@ -331,6 +350,30 @@ __device__ inline float wave_sum8_t(const float (&v)[8], int lane) {
     return octet_sum(keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), 0x128, 0xf, 0xf, false)));
 }
 
+// The same transposed totals of v[0..7] for FP64 sums (a virial's nine by eight separate sums and bpermutes took
+// about 160 instructions and 108 LDS operations an item).
+__device__ inline double item_sum8_t(const double (&v)[9], int lane) {
+    double g[4], h[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v[k]), __double2loint(v[k + 4]), false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v[k]), __double2hiint(v[k + 4]), false, false);
+        g[k] = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(g[k]), __double2loint(g[k + 2]), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(g[k]), __double2hiint(g[k + 2]), false, false);
+        h[k] = __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+    }
+    const bool odd8 = (lane >> 3) & 1;
+    double s = (odd8 ? h[1] : h[0]) + dpp_move<0x128, 0xf>(odd8 ? h[0] : h[1]);
+    s += dpp_move<0xB1, 0xf>(s);
+    s += dpp_move<0x4E, 0xf>(s);
+    s += dpp_move<0x141, 0xf>(s);
+    return s;
+}
+
 // One work item of the direct kernel: up to 32 j-entries of one i-cluster on
 // one wavefront (lane = entry slot x j-particle), i-forces in registers.
 // (Issuing a pass's j-force atomics after the next pass's loads, so that the
@@ -430,15 +473,29 @@ __device__ inline void force_item(const ForceArgs &a, const SysView &v, const fl
         }
     }
     }
-    if (ENER || VIR) {
-        acc_t out[kNAcc];
-        out[0] = ENER ? wave_sum(elj) * (acc_t)kLJScale : (acc_t)0;
-        out[1] = ENER ? wave_sum(ec) : (acc_t)0;
+    // energies and virial of the item (virial slots are read only with the virial)
+    const auto store = [&](int k, acc_t x) { v.partials[(size_t)k * v.pstride + v.pbase + item] = (double)x; };
+    if (VIR) {
 #pragma unroll
-        for (int k = 0; k < 9; ++k) out[2 + k] = VIR ? wave_sum(vir[k]) + viri[k] : (acc_t)0;
-        if (lane == 63)   // the lane that holds the i-force terms (virial slots are read only with the virial)
-            for (int k = 0; k < (VIR ? kNAcc : 2); ++k)
-                v.partials[(size_t)k * v.pstride + v.pbase + item] = (double)out[k];
+        for (int k = 0; k < 9; ++k) vir[k] += viri[k];   // zero but in lane 63
+        if constexpr (ACC64) {
+            const double tot = item_sum8_t(vir, lane), last = item_sum(vir[8]);
+            if ((lane & 7) == 0) store(2 + (lane >> 3), tot);
+            if (lane == 63) store(10, last);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) {
+                const acc_t tot = item_sum(vir[k]);
+                if (lane == 63) store(2 + k, tot);
+            }
+        }
+    }
+    if (ENER) {
+        const acc_t l = item_sum(elj) * (acc_t)kLJScale, c = item_sum(ec);
+        if (lane == 63) {
+            store(0, l);
+            store(1, c);
+        }
     }
 }
 
@@ -764,19 +821,48 @@ __device__ inline void fold_body(const FoldView &v, int cj, int lane) {
     }
 }
 
-// Energy and virial from the per-item partials, deterministic and in two
-// stages: the first kReduceParts fold workgroups each sum a contiguous share
-// of the items (fixed thread assignment and tree) into one value per
-// quantity, then one wavefront sums those values in a fixed order.  (A single
-// launch with a last-workgroup ticket needs a device-scope release per
-// workgroup, which writes back the L2 of every XCD: measured far slower.)
-// FP64, or FP32 throughout for the precision study.
+// Energy and virial from the per-item partials, deterministic.  FP64: the
+// first workgroups of the fold launch total one quantity each, beside the
+// workgroups that fold (a launch of its own for a last stage cost 4.7 us of
+// the 111 us call at 96 000 atoms, and a last-workgroup ticket needs a
+// device-scope release per workgroup, which writes back the L2 of every XCD:
+// 136 us).  One workgroup reads about 10 GB/s, so beyond kShareItems work
+// items it would outlast the fold (3 million atoms: 880 us against 701); the
+// items are then split into shares of that size and a second launch adds the
+// shares' totals.  FP32 throughout, for the precision study, keeps short
+// chains of sums, in two stages: the first kReduceParts fold workgroups each
+// sum a contiguous share of the items, then one wavefront those values in a
+// fixed order.
+constexpr long kShareItems = 49152;
+
+__device__ inline void total_partial(gptr<const double> p, long first, long nit, double *out) {
+    __shared__ double red[4];
+    const int t = threadIdx.x;
+    double s = 0.0;
+    long i = first + t;
+    for (; i + 15 * 256 < nit; i += 16 * 256) {   // sixteen loads in flight
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = p[i + u * 256];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) s += v[u];
+    }
+    double v[15];
+#pragma unroll
+    for (int u = 0; u < 15; ++u) v[u] = i + u * 256 < nit ? p[i + u * 256] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 15; ++u) s += v[u];
+    s = item_sum(s);
+    if ((t & 63) == 63) red[t >> 6] = s;
+    __syncthreads();
+    if (t == 0) *out = ((red[0] + red[1]) + red[2]) + red[3];
+}
+
 constexpr int kReduceParts = 256;
 static_assert(kReduceParts % 64 == 0, "the second stage gives each lane the same number of shares");
 
-template <bool ACC64>
 __device__ inline void fold_energy(const ForceArgs &a) {
-    using acc_t = typename std::conditional<ACC64, double, float>::type;
+    using acc_t = float;
     __shared__ acc_t red[256];
     const int t = threadIdx.x, w = blockIdx.x;
     const int R = min((int)gridDim.x, kReduceParts);
@@ -835,9 +921,21 @@ __global__ __launch_bounds__(256) void k_fold(ForceArgs a) {
                      (gptr<const float>)a.fj,   (gptr<const float4>)a.fi,  a.f_out,
                      a.parts,                   a.accumulate,              a.sci > 1 ? a.sci : 1,
                      a.flags};
-    fold_body<M, N>(v, blockIdx.x * 4 + (threadIdx.x >> 6), threadIdx.x & 63);
-    if (ACC == 1) fold_energy<false>(a);
-    if (ACC == 2) fold_energy<true>(a);
+    int blk = blockIdx.x;
+    if (ACC == 2) {
+        const int ne = (2 * a.ener + 9 * a.vir) * a.shares;
+        if (blk < ne) {
+            const int q = blk / a.shares, w = blk % a.shares, k = a.ener ? q : q + 2;
+            const long nit = a.totals[2], per = (nit + a.shares - 1) / a.shares, i0 = w * per;
+            total_partial((gptr<const double>)(a.partials + (size_t)k * a.pstride), i0, min(i0 + per, nit),
+                          a.shares > 1 ? a.blockpart + (size_t)k * kReduceParts + w
+                                       : (k < 2 ? a.energy + k : a.virial + k - 2));
+            return;
+        }
+        blk -= ne;
+    }
+    fold_body<M, N>(v, blk * 4 + (threadIdx.x >> 6), threadIdx.x & 63);
+    if (ACC == 1) fold_energy(a);
 }
 
 // Pair statistics of a list at the current positions (the paper's effective
@@ -896,8 +994,9 @@ void launch_fold(const ForceArgs &a, int acc, int nb, hipStream_t st) {
         k_fold<M, N, 1><<<nb, 256, 0, st>>>(a);
         k_reduce_parts<false><<<1, 64, 0, st>>>(a.blockpart, R, a.energy, a.virial, a.ener, a.vir);
     } else {
-        k_fold<M, N, 2><<<nb, 256, 0, st>>>(a);
-        k_reduce_parts<true><<<1, 64, 0, st>>>(a.blockpart, R, a.energy, a.virial, a.ener, a.vir);
+        k_fold<M, N, 2><<<nb + (2 * a.ener + 9 * a.vir) * a.shares, 256, 0, st>>>(a);
+        if (a.shares > 1)
+            k_reduce_parts<true><<<1, 64, 0, st>>>(a.blockpart, a.shares, a.energy, a.virial, a.ener, a.vir);
     }
 }
 
@@ -1117,12 +1216,24 @@ __global__ __launch_bounds__(512) void k_batch_tail(ForceArgs a, BatchArgs b, lo
                                           threadIdx.x & 63);
 }
 
-// one wavefront per j-cluster of every replica (the replicas' slot capacities
-// are multiples of N, so wavefront w covers global slots w*N .. w*N + N - 1)
+// One wavefront per j-cluster of every replica (the replicas' slot capacities
+// are multiples of N, so wavefront w covers global slots w*N .. w*N + N - 1).
+// The first n_rep * ne workgroups (ne quantities: the energies, the virial)
+// total one quantity of one replica each instead.
 template <int M, int N>
-__global__ __launch_bounds__(256) void k_batch_fold(BatchArgs b) {
-    const long total = b.slot_off[b.n_rep], first = (long)blockIdx.x * 4 * N;
-    const long g0 = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * N;
+__global__ __launch_bounds__(256) void k_batch_fold(BatchArgs b, int ener, int vir) {
+    const int ne = 2 * ener + 9 * vir;
+    int blk = blockIdx.x;
+    if (blk < b.n_rep * ne) {
+        const int r = blk / ne, q = blk % ne, k = ener ? q : q + 2;
+        const RepDesc &d = b.rep[r];
+        total_partial((gptr<const double>)(b.partials + (size_t)k * b.pstride + d.pbase), 0, d.totals[2],
+                      k < 2 ? b.energy + 2 * r + k : b.virial + 9 * r + k - 2);
+        return;
+    }
+    blk -= b.n_rep * ne;
+    const long total = b.slot_off[b.n_rep], first = (long)blk * 4 * N;
+    const long g0 = ((long)blk * 4 + (threadIdx.x >> 6)) * N;
     if (first >= total) return;   // whole workgroup past the end
     const int r = __builtin_amdgcn_readfirstlane(block_rep(b.slot_off, b.n_rep, first, min(g0, total - 1)));
     if (g0 >= total) return;
@@ -1133,30 +1244,6 @@ __global__ __launch_bounds__(256) void k_batch_fold(BatchArgs b) {
                      d.parts,                   b.accumulate,              1,
                      b.flags};
     fold_body<M, N>(v, (int)((g0 - b.slot_off[r]) / N), threadIdx.x & 63);
-}
-
-// one workgroup per replica: its energies (and virial) from the per-item partials, in a fixed order
-__global__ __launch_bounds__(256) void k_batch_reduce(BatchArgs b, int ener, int vir) {
-    __shared__ double red[256];
-    const int r = blockIdx.x, t = threadIdx.x;
-    const RepDesc &d = b.rep[r];
-    const int n = d.totals[2];
-    for (int k = 0; k < kNAcc; ++k) {
-        if ((k < 2 && !ener) || (k >= 2 && !vir)) continue;
-        double s = 0.0;
-        for (int i = t; i < n; i += 256) s += b.partials[(size_t)k * b.pstride + d.pbase + i];
-        red[t] = s;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if (t < w) red[t] += red[t + w];
-            __syncthreads();
-        }
-        if (t == 0) {
-            if (k < 2) b.energy[2 * r + k] = red[0];
-            else b.virial[9 * r + k - 2] = red[0];
-        }
-        __syncthreads();
-    }
 }
 
 template <int M, int N, bool E, bool V, int ELEC>
@@ -1409,6 +1496,8 @@ int launch_forces(nb_ctx *ctx, const nb_grid *g, const nb_list *l, const float *
         a.virial = virial;
         a.ener = (flags & NB_ENERGY) ? 1 : 0;
         a.vir = (flags & NB_VIRIAL) ? 1 : 0;
+        const long est = S || l->est_items <= 0 ? cap_items : std::min(cap_items, l->est_items);
+        a.shares = (int)std::min<long>(kReduceParts, (est + kShareItems - 1) / kShareItems);
     }
     k_gather<<<(g->slots_cap + 255) / 256, 256, 0, st>>>(a);
     const long nwaves = cap_items;
@@ -1495,13 +1584,12 @@ int launch_batch(nb_ctx *ctx, nb_batch *bt, const nb_params *p, unsigned flags, 
         else if (bt->m == 8 && bt->nn == 4) launch_batch_shape<8, 4>(a, b, flags, est, lds, st);
         else launch_batch_shape<8, 8>(a, b, flags, est, lds, st);
     }
-    const int nfold = (int)((bt->total_slots / bt->nn + 3) / 4);
-    if (bt->m == 4 && bt->nn == 4) k_batch_fold<4, 4><<<nfold, 256, 0, st>>>(b);
-    else if (bt->m == 4 && bt->nn == 8) k_batch_fold<4, 8><<<nfold, 256, 0, st>>>(b);
-    else if (bt->m == 8 && bt->nn == 4) k_batch_fold<8, 4><<<nfold, 256, 0, st>>>(b);
-    else k_batch_fold<8, 8><<<nfold, 256, 0, st>>>(b);
-    if (flags & (NB_ENERGY | NB_VIRIAL))
-        k_batch_reduce<<<bt->n_rep, 256, 0, st>>>(b, (flags & NB_ENERGY) != 0, (flags & NB_VIRIAL) != 0);
+    const int ener = (flags & NB_ENERGY) != 0, vir = (flags & NB_VIRIAL) != 0;
+    const int nfold = (int)((bt->total_slots / bt->nn + 3) / 4) + bt->n_rep * (2 * ener + 9 * vir);
+    if (bt->m == 4 && bt->nn == 4) k_batch_fold<4, 4><<<nfold, 256, 0, st>>>(b, ener, vir);
+    else if (bt->m == 4 && bt->nn == 8) k_batch_fold<4, 8><<<nfold, 256, 0, st>>>(b, ener, vir);
+    else if (bt->m == 8 && bt->nn == 4) k_batch_fold<8, 4><<<nfold, 256, 0, st>>>(b, ener, vir);
+    else k_batch_fold<8, 8><<<nfold, 256, 0, st>>>(b, ener, vir);
     MXN_HIP(hipGetLastError());
     return NB_OK;
 }
