@@ -89,6 +89,7 @@ struct ForceArgs {
     double *partials;
     float *f_out;
     int accumulate;
+    int own;          // no gather: the force kernel reads the caller's positions, the fold checks them
     int *flags;
     long pstride;     // partials layout: [kNAcc][pstride]
 };
@@ -103,6 +104,13 @@ __device__ inline float4 apply_image(float4 p, int im, float Lx, float Ly, float
     p.y = __fsub_rn(p.y, __fmul_rn((float)(((im >> 10) & 1023) - 512), Ly));
     p.z = __fsub_rn(p.z, __fmul_rn((float)(((im >> 20) & 1023) - 512), Lz));
     return p;
+}
+
+// The particle of a slot at the evaluated time, as the gather would store it (any particle for a dummy slot,
+// which takes part in no pair).
+__device__ inline float4 own_particle(const ForceArgs &a, int s) {
+    const int o = max(((gptr<const int>)a.perm)[s], 0);
+    return apply_image(ld((gptr<const float4>)a.xyzq_now + o), ((gptr<const int>)a.img_s)[s], a.Lx, a.Ly, a.Lz);
 }
 
 __global__ void k_gather(ForceArgs a) {
@@ -379,7 +387,9 @@ __device__ inline double item_sum8_t(const double (&v)[9], int lane) {
 // (Issuing a pass's j-force atomics after the next pass's loads, so that the
 // in-order wait for those loads does not include them, measured slower on
 // gfx950: it costs registers and occupancy for no gain.)
-template <int M, int N, bool ENER, bool VIR, bool ACC64, int ELEC, bool LM = true>
+// OWN (small systems): particles are read through the permutation and moved to
+// their image here, with the gather's own operations, instead of from xs_now.
+template <int M, int N, bool ENER, bool VIR, bool ACC64, int ELEC, bool LM = true, bool OWN = false>
 __device__ inline void force_item(const ForceArgs &a, const SysView &v, const float4 *ljt, const float2 *tab,
                                   const float4 *svec, int item, int lane) {
     using acc_t = typename std::conditional<ACC64, double, float>::type;
@@ -395,7 +405,7 @@ __device__ inline void force_item(const ForceArgs &a, const SysView &v, const fl
     unsigned ireal = 0;   // i-slots holding particles (dummies have type -1)
 #pragma unroll
     for (int k = 0; k < M; ++k) {
-        const float4 p = ld(v.xs_now + ci * M + k);
+        const float4 p = OWN ? own_particle(a, ci * M + k) : ld(v.xs_now + ci * M + k);
         xi[k] = p.x; yi[k] = p.y; zi[k] = p.z;
         qi[k] = p.w * a.coulomb_f;
         const int t = v.type_s[ci * M + k];
@@ -419,7 +429,7 @@ __device__ inline void force_item(const ForceArgs &a, const SysView &v, const fl
         const nb_jentry en = ld(v.entries + (valid ? e : e0));
         const int row = v.jpos[valid ? e : e0];
         const int jslot = en.cj * N + jb;
-        const float4 pj = ld(v.xs_now + jslot);
+        const float4 pj = OWN ? own_particle(a, jslot) : ld(v.xs_now + jslot);
         const int tjr = v.type_s[jslot];
         const int tj = lj_joff(a, tjr);
         const float4 sv = svec[en.shift];
@@ -499,7 +509,7 @@ __device__ inline void force_item(const ForceArgs &a, const SysView &v, const fl
     }
 }
 
-template <int M, int N, bool ENER, bool VIR, bool ACC64, int ELEC>
+template <int M, int N, bool ENER, bool VIR, bool ACC64, int ELEC, bool OWN>
 __global__ __launch_bounds__(256) void k_forces(ForceArgs a) {
     const long total = a.totals[2];
     if (xcd_block_first(total, 4) < 0) return;   // whole workgroup past the end
@@ -518,7 +528,7 @@ __global__ __launch_bounds__(256) void k_forces(ForceArgs a) {
     const long item = xcd_item(total, 4, threadIdx.x >> 6);
     if (item < 0) return;
     const SysView v = make_view(a.xs_now, a.type_s, a.fj, a.fi, a.jpos, a.items, a.entries, a.partials, a.pstride, 0);
-    force_item<M, N, ENER, VIR, ACC64, ELEC>(a, v, ljt, tab, svec, (int)item, lane);
+    force_item<M, N, ENER, VIR, ACC64, ELEC, true, OWN>(a, v, ljt, tab, svec, (int)item, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -914,6 +924,17 @@ __global__ __launch_bounds__(64) void k_reduce_parts(const double *blockpart, in
     }
 }
 
+// What the gather checks, for calls without one: every particle's coordinates and type.
+__device__ inline void check_slots(const ForceArgs &a, int first, int n) {
+    const int s = first + (threadIdx.x & 63);
+    if ((int)(threadIdx.x & 63) >= n || s >= *a.nslots) return;
+    const int o = a.perm[s];
+    if (o < 0) return;
+    const float4 p = a.xyzq_now[o];
+    if (!(isfinite(p.x) && isfinite(p.y) && isfinite(p.z) && isfinite(p.w))) atomicOr(a.flags, mxn::FLAG_NONFINITE);
+    if (a.type_s[s] >= a.nt) atomicOr(a.flags, mxn::FLAG_TYPE);
+}
+
 template <int M, int N, int ACC>   // ACC: 0 no energy/virial, 1 FP32, 2 FP64 sums
 __global__ __launch_bounds__(256) void k_fold(ForceArgs a) {
     const FoldView v{(gptr<const int>)a.nslots, (gptr<const int>)a.perm,   (gptr<const int>)a.totals,
@@ -934,6 +955,7 @@ __global__ __launch_bounds__(256) void k_fold(ForceArgs a) {
         }
         blk -= ne;
     }
+    if (a.own) check_slots(a, (blk * 4 + (threadIdx.x >> 6)) * N, N);
     fold_body<M, N>(v, blk * 4 + (threadIdx.x >> 6), threadIdx.x & 63);
     if (ACC == 1) fold_energy(a);
 }
@@ -1000,16 +1022,15 @@ void launch_fold(const ForceArgs &a, int acc, int nb, hipStream_t st) {
     }
 }
 
-template <int M, int N, bool E, bool V, bool D>
-void launch_k(const ForceArgs &a, int nb, size_t lds, int variant, hipStream_t st) {
-    (void)variant;   // direct (also for lists the super-cluster kernel does not take)
-    (void)lds;       // its LJ and shift tables are static LDS; only the Ewald table is dynamic
+template <int M, int N, bool E, bool V, bool D, bool OWN>
+void launch_k(const ForceArgs &a, int nb, hipStream_t st) {
+    // the LJ and shift tables are static LDS; only the Ewald table is dynamic
     if (a.elec == NB_COULOMB_RF)
-        k_forces<M, N, E, V, D, 1><<<nb, 256, 0, st>>>(a);
+        k_forces<M, N, E, V, D, 1, OWN><<<nb, 256, 0, st>>>(a);
     else if (a.elec == NB_COULOMB_EWALD_TABLE)
-        k_forces<M, N, E, V, D, 2><<<nb, 256, (size_t)a.ntab * sizeof(float2), st>>>(a);
+        k_forces<M, N, E, V, D, 2, OWN><<<nb, 256, (size_t)a.ntab * sizeof(float2), st>>>(a);
     else
-        k_forces<M, N, E, V, D, 0><<<nb, 256, 0, st>>>(a);
+        k_forces<M, N, E, V, D, 0, OWN><<<nb, 256, 0, st>>>(a);
 }
 
 template <int S, bool E, bool V, bool D>
@@ -1039,16 +1060,28 @@ void launch_sci(const ForceArgs &a, const nb_list *l, unsigned flags, int nb, si
     else launch_sci_k<S, false, false, true>(a, se, sm, si, nb, lds, st);
 }
 
+template <int M, int N, bool OWN>
+void launch_flags(const ForceArgs &a, unsigned flags, int nb, hipStream_t st) {
+    const bool E = flags & NB_ENERGY, V = flags & NB_VIRIAL;
+    if (E && V) launch_k<M, N, true, true, true, OWN>(a, nb, st);
+    else if (E) launch_k<M, N, true, false, true, OWN>(a, nb, st);
+    else if (V) launch_k<M, N, false, true, true, OWN>(a, nb, st);
+    else launch_k<M, N, false, false, true, OWN>(a, nb, st);
+}
+
+// direct kernel (also for lists the super-cluster kernel does not take)
 template <int M, int N>
-void launch_shape(const ForceArgs &a, unsigned flags, int nb, size_t lds, int var, hipStream_t st) {
-    const bool E = flags & NB_ENERGY, V = flags & NB_VIRIAL, D = !(flags & NB_ACC_FP32);
-    if (E && V && D) launch_k<M, N, true, true, true>(a, nb, lds, var, st);
-    else if (E && V) launch_k<M, N, true, true, false>(a, nb, lds, var, st);
-    else if (E && D) launch_k<M, N, true, false, true>(a, nb, lds, var, st);
-    else if (E) launch_k<M, N, true, false, false>(a, nb, lds, var, st);
-    else if (V && D) launch_k<M, N, false, true, true>(a, nb, lds, var, st);
-    else if (V) launch_k<M, N, false, true, false>(a, nb, lds, var, st);
-    else launch_k<M, N, false, false, true>(a, nb, lds, var, st);
+void launch_shape(const ForceArgs &a, unsigned flags, int nb, hipStream_t st) {
+    const bool E = flags & NB_ENERGY, V = flags & NB_VIRIAL;
+    if ((flags & NB_ACC_FP32) && (E || V)) {
+        if (E && V) launch_k<M, N, true, true, false, false>(a, nb, st);
+        else if (E) launch_k<M, N, true, false, false, false>(a, nb, st);
+        else launch_k<M, N, false, true, false, false>(a, nb, st);
+    } else if (a.own) {
+        launch_flags<M, N, true>(a, flags, nb, st);
+    } else {
+        launch_flags<M, N, false>(a, flags, nb, st);
+    }
 }
 
 
@@ -1390,6 +1423,12 @@ void set_ewald_poly(ForceArgs &a, float beta) {
     }
 }
 
+// Systems up to this many slots take no gather launch (2.3 us and the gap behind it): their force kernel reads
+// the particles through the permutation, one more load in the chain of a wavefront that has little to overlap it
+// with anyway.  900 atoms 16.8 -> 15.7 us a call, 12 000 (8x4) 29.1 -> 28.5; at 24 000 (4x8) 40.2 -> 42.0, and at
+// 96 000 the extra load costs 13 us.
+constexpr int kOwnSlots = 16384;
+
 // Device memory that exists from load time on, for nb_forces_noalloc: the per-work-item energy/virial
 // partials and, after them, the per-share sums of their reduction.  One copy per GPU, held until the
 // process ends; every call on a GPU shares it (calls that overlap in time on one GPU race).
@@ -1499,7 +1538,8 @@ int launch_forces(nb_ctx *ctx, const nb_grid *g, const nb_list *l, const float *
         const long est = S || l->est_items <= 0 ? cap_items : std::min(cap_items, l->est_items);
         a.shares = (int)std::min<long>(kReduceParts, (est + kShareItems - 1) / kShareItems);
     }
-    k_gather<<<(g->slots_cap + 255) / 256, 256, 0, st>>>(a);
+    a.own = !S && !(need_acc && (flags & NB_ACC_FP32)) && g->slots_cap <= kOwnSlots;
+    if (!a.own) k_gather<<<(g->slots_cap + 255) / 256, 256, 0, st>>>(a);
     const long nwaves = cap_items;
     int nb = (int)((nwaves + 3) / 4);
     nb = (nb + 7) / 8 * 8;
@@ -1507,13 +1547,12 @@ int launch_forces(nb_ctx *ctx, const nb_grid *g, const nb_list *l, const float *
     const size_t lds = (32 + (size_t)p->ntypes * p->ntypes + 1) * sizeof(float4);
     {
         ScopedTimer tm(ctx, noalloc ? -1 : NB_TIMER_FORCE_KERNEL);
-        const int var = noalloc ? NB_FORCE_DIRECT : ctx->force_variant;
         if (S == 8) launch_sci<8>(a, l, flags, nb, lds, st);
         else if (S == 4) launch_sci<4>(a, l, flags, nb, lds, st);
-        else if (g->m == 4 && g->nn == 4) launch_shape<4, 4>(a, flags, nb, lds, var, st);
-        else if (g->m == 4 && g->nn == 8) launch_shape<4, 8>(a, flags, nb, lds, var, st);
-        else if (g->m == 8 && g->nn == 4) launch_shape<8, 4>(a, flags, nb, lds, var, st);
-        else launch_shape<8, 8>(a, flags, nb, lds, var, st);
+        else if (g->m == 4 && g->nn == 4) launch_shape<4, 4>(a, flags, nb, st);
+        else if (g->m == 4 && g->nn == 8) launch_shape<4, 8>(a, flags, nb, st);
+        else if (g->m == 8 && g->nn == 4) launch_shape<8, 4>(a, flags, nb, st);
+        else launch_shape<8, 8>(a, flags, nb, st);
     }
     const int acc = !need_acc ? 0 : ((flags & NB_ACC_FP32) ? 1 : 2);
     if (g->m == 4 && g->nn == 4) launch_fold<4, 4>(a, acc, nfold, st);
