@@ -434,7 +434,7 @@ int nb_pairlist_build(nb_ctx *c, const nb_grid *g, float rlist, float rbb, const
     rc = rc ? rc : ensure(l->ctx, l->part_count, nreg * 4);
     rc = rc ? rc : ensure(l->ctx, l->part_start, nreg * 4);
     rc = rc ? rc : ensure(l->ctx, l->part_istart, nreg * 4);
-    rc = rc ? rc : ensure(l->ctx, l->totals, 16);
+    rc = rc ? rc : ensure(l->ctx, l->totals, 32);
     // entry and item capacities are set by the reserving (synchronous) build
     if (rc == NB_OK) {
         ScopedTimer tm(c, NB_TIMER_PAIRLIST);
@@ -778,7 +778,12 @@ int nb_batch_create(nb_ctx *c, int n_rep, nb_grid *const *grids, nb_list *const 
     int ncu = 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || ncu < 1) ncu = 1;
     b->ncu = ncu;
-    int rc = batch_refresh(b, xyzq_now, f, true);
+    int rc = NB_OK;
+    for (int r = 0; r < n_rep && rc == NB_OK; ++r) {
+        lists[r]->batched = true;
+        rc = launch_full_items(lists[r]);
+    }
+    rc = rc ? rc : batch_refresh(b, xyzq_now, f, true);
     if (rc != NB_OK) {
         nb_batch_free(b);
         return rc;

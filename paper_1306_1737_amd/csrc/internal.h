@@ -31,8 +31,8 @@ int fail(int status, const std::string &msg);
 // bits latched by kernels in ctx->d_flags
 enum : int { FLAG_NONFINITE = 1, FLAG_OVERFLOW = 2, FLAG_FORCE_RANGE = 4, FLAG_TYPE = 8 };
 
-// work items of the force kernel hold at most this many j-entries of one i-cluster
-// Entries per force work item: four wavefront passes of 64/N entries each.
+// Entries per force work item (of one i-cluster): four wavefront passes of 64/N entries each.  Lists so short that
+// smaller items still find a free wavefront slot each take one or two passes (nb_list::per_item).
 constexpr int item_entries(int n) { return 256 / n; }
 constexpr int kHistAtoms = 4096;         // particles per workgroup in the column histogram
 constexpr int kMaxHistColumns = 16384;   // larger grids count columns with global atomics
@@ -168,6 +168,8 @@ struct nb_list {
     int resv_parts = 0;        // search parts of the reserved layout (0: none yet)
     int resv_nci = 0;          // i-cluster capacity of the reserved layout
     long resv_size = 0;        // entries per region of the reserved layout
+    int per_item = 0;          // entries per work item of the reserved layout
+    bool batched = false;      // bound to a batch, which fills the GPU with full items
     long est_items = 0;        // work items of the last synchronous build (sizes the force-kernel grid)
     long cap_rows = 0;         // j-force rows fj holds: the last synchronous build's entries plus a quarter
     long last_entries = 0;     // host copy after a synchronous build
@@ -265,6 +267,8 @@ int launch_mlp_infer(nb_ctx *ctx, const nb_mlp *mlp, const float *X, int batch, 
 
 // kernel launchers (grid.hip, pairlist.hip, forces.hip)
 int launch_grid_sort(nb_grid *g, const float *xyzq, const int *type);
+// work items of full length for a list built with shorter ones (entries and regions stay as they are)
+int launch_full_items(nb_list *l);
 int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool sync, bool by_distance);
 // noalloc: the device address of the static scratch (nb_forces_noalloc), or null
 int launch_forces(nb_ctx *ctx, const nb_grid *g, const nb_list *l, const float *xyzq_now, const nb_params *p,

@@ -423,33 +423,37 @@ __global__ __launch_bounds__(64) void k_sort_entries(const int *part_start, cons
     }
 }
 
-// Region counts of a count pass (one workgroup of 1024 threads).  out[0]: the largest region count;
-// out[1]: the work items the counts make (per_item entries each); out[2]: the entries (the list's
-// totals[2] is set again by its fill pass, before any force call reads it).
+// Region counts of a count pass (one workgroup of 1024 threads).  out[0]: the largest region count; out[2]: the
+// entries; out[1], out[4], out[5]: the work items the counts make with full items (per_item entries), halves and
+// quarters (the list's totals[1] and [2] are set again by its fill pass, before any force call reads them).
 __global__ __launch_bounds__(1024) void k_max_count(const int *in, int n, int per_item, int *out) {
-    __shared__ int m[1024], c[1024], e[1024];
-    int v = 0, it = 0, en = 0;
-    for (int i = threadIdx.x; i < n; i += 1024) {
-        v = max(v, in[i]);
-        it += (in[i] + per_item - 1) / per_item;
-        en += in[i];
+    __shared__ int red[5][1024];
+    const int t = threadIdx.x;
+    int v[5] = {0, 0, 0, 0, 0};   // largest, entries, items of three lengths
+    for (int i = t; i < n; i += 1024) {
+        const int c = in[i];
+        v[0] = max(v[0], c);
+        v[1] += c;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) v[2 + k] += (c + (per_item >> k) - 1) / (per_item >> k);
     }
-    m[threadIdx.x] = v;
-    c[threadIdx.x] = it;
-    e[threadIdx.x] = en;
+#pragma unroll
+    for (int k = 0; k < 5; ++k) red[k][t] = v[k];
     __syncthreads();
-    for (unsigned s = 512; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            m[threadIdx.x] = max(m[threadIdx.x], m[threadIdx.x + s]);
-            c[threadIdx.x] += c[threadIdx.x + s];
-            e[threadIdx.x] += e[threadIdx.x + s];
+    for (int s = 512; s > 0; s >>= 1) {
+        if (t < s) {
+            red[0][t] = max(red[0][t], red[0][t + s]);
+#pragma unroll
+            for (int k = 1; k < 5; ++k) red[k][t] += red[k][t + s];
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        out[0] = m[0];
-        out[1] = c[0];
-        out[2] = e[0];
+    if (t == 0) {
+        out[0] = red[0][0];
+        out[1] = red[2][0];
+        out[2] = red[1][0];
+        out[4] = red[3][0];
+        out[5] = red[4][0];
     }
 }
 
@@ -518,6 +522,15 @@ __global__ __launch_bounds__(1024) void k_finish(int nregions, int per_item, con
     } else {
         mxn::scan_body(jcount, jstart, njc, 0, 1, nullptr, nullptr, jcount);
     }
+}
+
+// Item offsets of full-length items over unchanged regions; an overflowed list (items, none usable) stays unusable.
+__global__ __launch_bounds__(1024) void k_full_items(int nregions, int per_item, const int *part_count,
+                                                     int *part_istart, int *totals) {
+    const bool usable = totals[2] > 0;
+    __syncthreads();   // read before the scan's thread 0 writes the totals
+    mxn::scan_body(part_count, part_istart, nregions, 2, per_item, totals + 1, totals);
+    if (threadIdx.x == 0 && usable) totals[2] = totals[1];
 }
 
 __global__ void k_items(int nparts_total, int parts, int per_item, const int *part_count, const int *part_start,
@@ -877,13 +890,13 @@ static JPosArgs make_jpos(const nb_list *l) {
 // usable count and j-cluster first rows of a list after its fill or prune pass
 static void finish_list(nb_list *l, int nregions, hipStream_t st) {
     const nb_grid *g = l->grid;
-    k_finish<<<2, 1024, 0, st>>>(nregions, item_entries(g->nn), (const int *)l->part_count.p,
+    k_finish<<<2, 1024, 0, st>>>(nregions, l->per_item, (const int *)l->part_count.p,
                                  (int *)l->part_istart.p, l->cap_items, l->cap_rows, (int *)l->totals.p,
                                  l->ctx->d_flags, (int *)l->jcount.p, (int *)l->jstart.p, g->slots_cap / g->nn);
 }
 // work items and each usable entry's row (after finish_list, and after the distance sort)
 static void finish_rows(nb_list *l, int nregions, int parts, hipStream_t st) {
-    k_items_rows<<<(nregions + 3) / 4, 256, 0, st>>>(nregions, parts, item_entries(l->grid->nn),
+    k_items_rows<<<(nregions + 3) / 4, 256, 0, st>>>(nregions, parts, l->per_item,
                                                      (const int *)l->part_count.p, (const int *)l->part_start.p,
                                                      (const int *)l->part_istart.p, l->cap_items,
                                                      (int4 *)l->items.p, (const int *)l->totals.p,
@@ -906,7 +919,7 @@ void fill_list_job(void *out, nb_list *l, const int *excl_off, const int *excl_i
     j.a.entries = (nb_jentry *)l->entries.p;
     j.a.keys = nullptr;
     j.nregions = l->resv_nci * l->resv_parts;
-    j.per_item = item_entries(l->grid->nn);
+    j.per_item = l->per_item;
     j.part_count = (int *)l->part_count.p;
     j.part_start = (int *)l->part_start.p;
     j.part_istart = (int *)l->part_istart.p;
@@ -945,6 +958,8 @@ int launch_pairlist_batch(hipStream_t st, int m, int nn, const void *jobs, const
     return NB_OK;
 }
 
+constexpr int kSmallItems = 8192;
+
 int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool sync, bool by_distance) {
     const nb_grid *g = l->grid;
     nb_ctx *ctx = l->ctx;
@@ -979,7 +994,7 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
         else run<8, 8>(l, a, false, nblocks, st);
         k_max_count<<<1, 1024, 0, st>>>((const int *)l->part_count.p, nregions, item_entries(g->nn),
                                          (int *)l->totals.p);
-        MXN_HIP(hipMemcpyAsync(ctx->h_pinned, l->totals.p, 3 * sizeof(int), hipMemcpyDeviceToHost, st));
+        MXN_HIP(hipMemcpyAsync(ctx->h_pinned, l->totals.p, 6 * sizeof(int), hipMemcpyDeviceToHost, st));
         MXN_HIP(hipMemsetAsync((int *)l->totals.p + 3, 0, sizeof(int), st));
         MXN_HIP(hipStreamSynchronize(st));
         const long mx = ctx->h_pinned[0];
@@ -991,7 +1006,20 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
             if (rc) return rc;
             l->cap_entries = ce;
         }
-        const long cit = ce / item_entries(g->nn) + nregions + 256;   // each region: at most count/per-item + 1 items
+        // Work items of one or two passes while every one of them finds a free wavefront slot (eight a SIMD): the
+        // GPU is not filled, and a shorter chain per wavefront ends sooner.  One pass against four: 900 atoms 8x8
+        // 12.1 against 15.8 us a call, 3000 (4x4) 20.1 against 21.6; 12 000 (8x4) two passes as four, one 6 %
+        // slower (15 k items); 24 000 and more four.  (The capacity bound keeps lists of very uneven regions, and
+        // so the scratch nb_forces_noalloc needs for them, as they were.)
+        const int full = item_entries(g->nn);
+        l->per_item = full;
+        l->est_items = ctx->h_pinned[1];
+        for (int k = 2; k > 0 && !l->batched && l->per_item == full; --k)
+            if (ctx->h_pinned[3 + k] <= kSmallItems && ce / (full >> k) + nregions <= 8 * kSmallItems) {
+                l->per_item = full >> k;
+                l->est_items = ctx->h_pinned[3 + k];
+            }
+        const long cit = ce / l->per_item + nregions + 256;   // each region: at most count/per-item + 1 items
         if (cit > l->cap_items) {
             int rc = ensure(l->ctx, l->items, (size_t)cit * sizeof(int4));
             if (rc) return rc;
@@ -1019,7 +1047,6 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
         l->resv_nci = nci_cap;
         l->last_entries = ce;
         l->resv_size = size;
-        l->est_items = ctx->h_pinned[1];
     }
     if (by_distance) {   // the fill pass writes canonical order and keys; the sort orders each region
         int rc = ensure(l->ctx, l->entries_canon, (size_t)l->cap_entries * sizeof(nb_jentry));
@@ -1048,6 +1075,19 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
                                                 (int *)l->jrank.p);
     finish_rows(l, nregions, parts, st);
     l->sci_valid = false;
+    MXN_HIP(hipGetLastError());
+    return NB_OK;
+}
+
+int launch_full_items(nb_list *l) {
+    if (l->resv_parts == 0 || l->per_item == 0 || l->per_item == item_entries(l->grid->nn)) return NB_OK;
+    l->per_item = item_entries(l->grid->nn);   // capacities hold: fewer items of the same entries
+    const int nregions = l->resv_nci * l->resv_parts;
+    k_full_items<<<1, 1024, 0, l->ctx->stream>>>(nregions, l->per_item, (const int *)l->part_count.p,
+                                                 (int *)l->part_istart.p, (int *)l->totals.p);
+    k_items<<<(nregions + 255) / 256, 256, 0, l->ctx->stream>>>(
+        nregions, l->resv_parts, l->per_item, (const int *)l->part_count.p, (const int *)l->part_start.p,
+        (const int *)l->part_istart.p, l->cap_items, (int4 *)l->items.p);
     MXN_HIP(hipGetLastError());
     return NB_OK;
 }
@@ -1135,7 +1175,7 @@ int launch_prune(nb_list *in, const nb_list *outer, float r) {
     int rc = ensure(in->ctx, in->part_count, nreg * 4);
     rc = rc ? rc : ensure(in->ctx, in->part_start, nreg * 4);
     rc = rc ? rc : ensure(in->ctx, in->part_istart, nreg * 4);
-    rc = rc ? rc : ensure(in->ctx, in->totals, 16);
+    rc = rc ? rc : ensure(in->ctx, in->totals, 32);
     rc = rc ? rc : ensure(in->ctx, in->entries, (size_t)outer->cap_entries * sizeof(nb_jentry));
     rc = rc ? rc : ensure(in->ctx, in->items, (size_t)outer->cap_items * sizeof(int4));
     rc = rc ? rc : ensure(in->ctx, in->jcount, (size_t)(njc + 1) * 4);
@@ -1156,6 +1196,7 @@ int launch_prune(nb_list *in, const nb_list *outer, float r) {
     in->resv_parts = outer->resv_parts;
     in->resv_nci = outer->resv_nci;
     in->last_entries = outer->last_entries;
+    in->per_item = outer->per_item;
     in->est_items = outer->est_items;
     in->cap_rows = outer->cap_rows;
     in->resv_size = outer->resv_size;
