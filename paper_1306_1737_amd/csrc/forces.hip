@@ -836,14 +836,14 @@ __device__ inline void fold_body(const FoldView &v, int cj, int lane) {
 // workgroups that fold (a launch of its own for a last stage cost 4.7 us of
 // the 111 us call at 96 000 atoms, and a last-workgroup ticket needs a
 // device-scope release per workgroup, which writes back the L2 of every XCD:
-// 136 us).  One workgroup reads about 10 GB/s, so beyond kShareItems work
-// items it would outlast the fold (3 million atoms: 880 us against 701); the
-// items are then split into shares of that size and a second launch adds the
+// 136 us).  One workgroup reads 10 to 20 GB/s, so beyond kShareItems work items
+// it would outlast the fold (3 million atoms: 880 us against 701; 50 000 items
+// are done within the fold's 19 us); the items are then split into shares of that size and a second launch adds the
 // shares' totals.  FP32 throughout, for the precision study, keeps short
 // chains of sums, in two stages: the first kReduceParts fold workgroups each
 // sum a contiguous share of the items, then one wavefront those values in a
 // fixed order.
-constexpr long kShareItems = 49152;
+constexpr long kShareItems = 65536;
 
 __device__ inline void total_partial(gptr<const double> p, long first, long nit, double *out) {
     __shared__ double red[4];
