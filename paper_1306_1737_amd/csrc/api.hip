@@ -398,7 +398,7 @@ int nb_grid_export(nb_grid *g, int *perm, float *xyzq, int *img, int *col_start,
 
 static void list_release(nb_list *l) {
     DevBuf *bufs[] = {&l->entries,    &l->entries_canon, &l->keys,        &l->items,  &l->part_count,
-                      &l->part_start, &l->part_istart,   &l->totals,      &l->jcount, &l->jstart,
+                      &l->part_start, &l->part_istart,   &l->totals,      &l->jcount, &l->joff, &l->jstart,
                       &l->jrank,      &l->jrank_canon,   &l->fj,          &l->fi,
                       &l->sci_ent,    &l->sci_mask,      &l->sci_count,   &l->sci_base, &l->sci_istart,
                       &l->sci_items,  &l->sci_jcount,    &l->sci_jstart,  &l->sci_totals, &l->sci_fi};
@@ -800,7 +800,7 @@ void nb_batch_free(nb_batch *b) {
     if (b->graph) (void)hipGraphDestroy(b->graph);
     if (b->capture_stream) (void)hipStreamDestroy(b->capture_stream);
     DevBuf *bufs[] = {&b->desc, &b->slot_off, &b->atom_off, &b->item_off, &b->partials,
-                      &b->gjobs, &b->ljobs, &b->goff,     &b->loff,     &b->scans};
+                      &b->gjobs, &b->ljobs, &b->goff,     &b->loff};
     for (DevBuf *d : bufs) release(*d);
     delete b;
 }
@@ -940,7 +940,6 @@ static int rebuild_refresh(nb_batch *b) {
     const size_t gs = grid_job_size(), ls = list_job_size();
     const int GS = grid_job_stages(), LS = list_job_stages();
     std::vector<char> gj(gs * n), lj(ls * n);
-    std::vector<ScanJob> sj(2 * n);   // item offsets, then j-cluster view offsets
     std::vector<int> goff(GS * (n + 1)), loff(LS * (n + 1)), gtot(GS, 0), ltot(LS, 0), gb(GS), lb(LS);
     int max_ncol = 1;
     for (int r = 0; r < n; ++r) {
@@ -950,7 +949,7 @@ static int rebuild_refresh(nb_batch *b) {
         if (l->resv_parts == 0 || l->resv_nci != g->slots_cap / g->m || l->grid != g)
             return fail(NB_ERR_STATE, "nb_batch_rebuild: every replica's list needs a synchronous build on its grid");
         fill_grid_job(gj.data() + gs * r, g, b->xyzq[r], b->type[r]);
-        fill_list_job(lj.data() + ls * r, l, b->excl_off[r], b->excl_idx[r], &sj[r], &sj[n + r]);
+        fill_list_job(lj.data() + ls * r, l, b->excl_off[r], b->excl_idx[r]);
         grid_job_blocks(g, gb.data());
         list_job_blocks(l, lb.data());
         for (int k = 0; k < GS; ++k) {
@@ -971,12 +970,10 @@ static int rebuild_refresh(nb_batch *b) {
     CHECK(ensure(b->ctx, b->ljobs, lj.size()));
     CHECK(ensure(b->ctx, b->goff, goff.size() * sizeof(int)));
     CHECK(ensure(b->ctx, b->loff, loff.size() * sizeof(int)));
-    CHECK(ensure(b->ctx, b->scans, sj.size() * sizeof(ScanJob)));
     MXN_HIP(hipMemcpy(b->gjobs.p, gj.data(), gj.size(), hipMemcpyHostToDevice));
     MXN_HIP(hipMemcpy(b->ljobs.p, lj.data(), lj.size(), hipMemcpyHostToDevice));
     MXN_HIP(hipMemcpy(b->goff.p, goff.data(), goff.size() * sizeof(int), hipMemcpyHostToDevice));
     MXN_HIP(hipMemcpy(b->loff.p, loff.data(), loff.size() * sizeof(int), hipMemcpyHostToDevice));
-    MXN_HIP(hipMemcpy(b->scans.p, sj.data(), sj.size() * sizeof(ScanJob), hipMemcpyHostToDevice));
     b->gjobs_host = gj;
     b->ljobs_host = lj;
     b->gtotal = gtot;
@@ -994,7 +991,7 @@ static int launch_rebuild(nb_ctx *c, nb_batch *b) {
     {
         ScopedTimer tm(c, NB_TIMER_PAIRLIST);
         CHECK(launch_pairlist_batch(c->stream, b->m, b->nn, b->ljobs.p, (const int *)b->loff.p, b->n_rep,
-                                    b->ltotal.data(), (const ScanJob *)b->scans.p));
+                                    b->ltotal.data()));
     }
     for (int r = 0; r < b->n_rep; ++r) {   // every replica's grid and list are now one generation newer
         ++b->grids[r]->generation;

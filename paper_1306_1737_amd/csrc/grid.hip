@@ -374,11 +374,6 @@ __global__ __launch_bounds__(kSortThreads) void kb_col_sort(const GridJob *J, co
     col_sort_body(J[r].s, blockIdx.x - off[r]);
 }
 
-__global__ __launch_bounds__(1024) void kb_scan(const mxn::ScanJob *J) {
-    const mxn::ScanJob &j = J[blockIdx.x];
-    scan_body(j.in, j.out, j.n, j.mode, j.p, j.total, j.raw_total, j.clear);
-}
-
 inline int blocks(long n, int t) { return (int)((n + t - 1) / t); }
 
 }  // namespace
@@ -446,9 +441,6 @@ int launch_grid_sort_batch(hipStream_t st, const void *jobs, const int *off, int
     MXN_HIP(hipGetLastError());
     return NB_OK;
 }
-
-// one exclusive scan per job, one workgroup each
-void launch_scan_batch(const ScanJob *jobs, int n_jobs, hipStream_t st) { kb_scan<<<n_jobs, 1024, 0, st>>>(jobs); }
 
 int launch_grid_sort(nb_grid *g, const float *xyzq, const int *type) {
     hipStream_t st = g->ctx->stream;

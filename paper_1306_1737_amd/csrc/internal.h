@@ -37,6 +37,9 @@ constexpr int item_entries(int n) { return 256 / n; }
 constexpr int kHistAtoms = 4096;         // particles per workgroup in the column histogram
 constexpr int kMaxHistColumns = 16384;   // larger grids count columns with global atomics
 inline int hist_blocks(int n) { return n < 1 ? 1 : (n + kHistAtoms - 1) / kHistAtoms; }
+constexpr int kRankSets = 2;         // sets of j-cluster rank counters
+inline int rank_stride(long njc) { return (int)((njc + 31) / 32 * 32); }   // a set's counters: whole 128-byte lines
+constexpr int kOneGroupTiles = 4;    // list finish: up to this many j-cluster tiles in one workgroup
 constexpr int kMaxSearchParts = 8;   // wavefronts that may share the pair search of one i-cluster
 constexpr int kMaxTypes = 32;
 
@@ -155,12 +158,13 @@ struct nb_list {
     mxn::DevBuf entries_canon, keys;   // fill-pass output before a distance sort, and its sort keys
     mxn::DevBuf part_count, part_start, part_istart;
     mxn::DevBuf totals;        // int[4]: entries, items, usable items (0 after an overflow), region overflow
-    // j-cluster view, rebuilt with the list: entries per j-cluster (counters,
-    // zero between builds), their exclusive scan (first row of each j-cluster),
-    // and for each entry position its rank among the j-cluster's entries,
-    // turned into its row jstart[cj] + rank by the build's last pass
-    // (jrank_canon: the fill pass's ranks before a distance sort)
-    mxn::DevBuf jcount, jstart, jrank, jrank_canon;
+    // j-cluster view, rebuilt with the list: entries per j-cluster (counters in
+    // kRankSets sets, zero between builds), each set's offset within the
+    // j-cluster (then the finish's tile sums), the first row of each j-cluster,
+    // and for each entry position its rank among the j-cluster's entries of its
+    // set, turned into its row by the build's last pass (jrank_canon: the fill
+    // pass's ranks before a distance sort)
+    mxn::DevBuf jcount, joff, jstart, jrank, jrank_canon;
     // force-call buffers: j-force (x, y, z) per (row, j-particle), rows grouped
     // by j-cluster, and float4 i-force per (work item, i-particle); summed per
     // cluster after the force kernel
@@ -201,7 +205,7 @@ struct nb_batch {
     std::vector<const int *> type, excl_off, excl_idx;
     bool topology = false;
     bool cycle = false;   // the captured graph holds the rebuild too
-    mxn::DevBuf gjobs, ljobs, goff, loff, scans;
+    mxn::DevBuf gjobs, ljobs, goff, loff;
     std::vector<char> gjobs_host, ljobs_host;   // job tables as last copied to the device
     std::vector<int> gtotal, ltotal;
     int max_ncol = 0;
@@ -239,14 +243,6 @@ int prepare_coulomb(nb_ctx *ctx, const nb_params *p);
 constexpr float kMaxTableRc = 4.0f;
 size_t rep_desc_size();
 // batched list rebuild (grid sort and pair search of many replicas, one launch per stage)
-struct ScanJob {
-    const int *in;
-    int *out;
-    int n, mode, p;
-    int *total, *raw_total;
-    int *clear;   // the input, zeroed once read (or null)
-};
-void launch_scan_batch(const ScanJob *jobs, int n_jobs, hipStream_t st);
 size_t grid_job_size();
 int grid_job_stages();
 bool grid_batchable(const nb_grid *g);
@@ -255,11 +251,9 @@ void grid_job_blocks(const nb_grid *g, int *blocks_per_stage);
 int launch_grid_sort_batch(hipStream_t st, const void *jobs, const int *off, int n_rep, const int *total, int max_ncol);
 size_t list_job_size();
 int list_job_stages();
-void fill_list_job(void *out, nb_list *l, const int *excl_off, const int *excl_idx, ScanJob *scan,
-                   ScanJob *jscan);
+void fill_list_job(void *out, nb_list *l, const int *excl_off, const int *excl_idx);
 void list_job_blocks(const nb_list *l, int *blocks_per_stage);
-int launch_pairlist_batch(hipStream_t st, int m, int nn, const void *jobs, const int *off, int n_rep, const int *total,
-                          const ScanJob *scans);
+int launch_pairlist_batch(hipStream_t st, int m, int nn, const void *jobs, const int *off, int n_rep, const int *total);
 void fill_rep_desc(void *out, const nb_grid *g, const nb_list *l, const float *xyzq_now, float *f, long pbase);
 int launch_mlp_step(nb_ctx *ctx, nb_mlp *mlp, const float *X, const float *y, int batch, float lr, float *loss,
                     float *grad_out);

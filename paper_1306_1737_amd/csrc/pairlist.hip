@@ -42,9 +42,9 @@ struct SearchArgsT {
     P<int> region_overflow;              // set when a region is too small
     P<nb_jentry> entries;   // each region in (shift, j-cluster) order
     P<float> keys;          // bounding-box distance^2 of each entry (or null)
-    P<int> jcount;          // entries per j-cluster (fill pass; zero before it)
-    P<int> jrank;           // each written entry's rank among its j-cluster's entries
-    int nci_cap, parts;
+    P<int> jcount;          // entries per j-cluster, kRankSets counters jstride apart (fill pass; zero before it)
+    P<int> jrank;           // each written entry's rank among its j-cluster's entries of the workgroup's set
+    int nci_cap, parts, jstride;
 };
 using SearchArgs = SearchArgsT<plain>;
 using SearchArgsG = SearchArgsT<gptr>;
@@ -74,9 +74,13 @@ __device__ inline SearchArgsG to_global(const SearchArgs &a) {
     g.keys = (gptr<float>)a.keys;
     g.jcount = (gptr<int>)a.jcount;
     g.jrank = (gptr<int>)a.jrank;
-    g.nci_cap = a.nci_cap; g.parts = a.parts;
+    g.nci_cap = a.nci_cap; g.parts = a.parts; g.jstride = a.jstride;
     return g;
 }
+
+// Each j-cluster has a rank counter in kRankSets sets; a workgroup counts in the set of its index (workgroups go to
+// the XCDs round-robin by index, so the workgroups of one XCD share a set).
+__device__ inline int rank_set(int blk) { return blk & (mxn::kRankSets - 1); }
 
 __device__ inline float sq3(float x, float y, float z) { return (x * x + y * y) + z * z; }
 
@@ -358,7 +362,7 @@ __device__ inline void search_body(const A &a, int blk) {
                         en.mhi = (uint32_t)(mask >> 32);
                         st(a.entries + wpos + rank, en);
                         if (a.keys) a.keys[wpos + rank] = d2;
-                        a.jrank[wpos + rank] = atomicAdd((int *)a.jcount + cj, 1);
+                        a.jrank[wpos + rank] = atomicAdd((int *)a.jcount + rank_set(blk) * a.jstride + cj, 1);
                     }
                 }
                 cnt += __popcll(accepted);
@@ -425,7 +429,7 @@ __global__ __launch_bounds__(64) void k_sort_entries(const int *part_start, cons
 
 // Region counts of a count pass (one workgroup of 1024 threads).  out[0]: the largest region count; out[2]: the
 // entries; out[1], out[4], out[5]: the work items the counts make with full items (per_item entries), halves and
-// quarters (the list's totals[1] and [2] are set again by its fill pass, before any force call reads them).
+// quarters.  out is pinned host memory.
 __global__ __launch_bounds__(1024) void k_max_count(const int *in, int n, int per_item, int *out) {
     __shared__ int red[5][1024];
     const int t = threadIdx.x;
@@ -457,10 +461,12 @@ __global__ __launch_bounds__(1024) void k_max_count(const int *in, int n, int pe
     }
 }
 
-// Uniform regions: region g starts at g * size (g = 0 .. n).
-__global__ void k_region_starts(int n, int size, int *start) {
+// Uniform regions (region g starts at g * size, g = 0 .. n), cleared j-cluster counters and overflow mark.
+__global__ void k_reserve(int n, int size, int *start, int njc, int *jcount, int *totals) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
     if (g <= n) start[g] = g * size;
+    for (int k = g; k < njc; k += gridDim.x * blockDim.x) jcount[k] = 0;
+    if (g == 0) totals[3] = 0;
 }
 
 // totals: [0] entries, [1] items (from the scan), [3] region overflow; writes
@@ -480,49 +486,199 @@ __device__ inline void finalize_body(int *totals, long cap_items, long cap_rows,
 // (instead of adding them to memory with atomics) in a row of a buffer whose
 // rows are grouped by j-cluster, so that the reduction reads each j-cluster's
 // rows contiguously.  The fill pass (and the prune) take each written entry's
-// rank among its j-cluster's entries from a counter per j-cluster; after the
-// build an exclusive scan of the counters (which clears them for the next
-// build) gives each j-cluster's first row, and this pass turns every usable
-// entry's rank into its row (the force kernel then reads one row index per
-// entry instead of a dependent gather of the j-cluster's start: measured
-// cheaper).  The row order within a j-cluster depends on timing; the
-// reduction sums in fixed point, so the forces do not.
-struct JPosArgs {
-    const int *totals;   // [2]: usable items
-    const int4 *items;
+// rank among its j-cluster's entries from a counter per j-cluster, in one of
+// kRankSets sets by workgroup (the 1.0 M atomics of the 96 000-atom search
+// contend for them: 51 us with one set, 45.7 with two, 44.2 with eight, whose
+// scan takes longer than that saves); after the
+// build the counters are scanned, sets within a j-cluster and j-clusters in
+// turn, into each j-cluster's first row and each set's offset in it (and
+// cleared for the next build), and a last pass turns every entry's rank into
+// its row (the force kernel then reads one row index per entry instead of
+// dependent gathers of the starts: measured cheaper).  The row order within a
+// j-cluster depends on timing; the reduction sums in fixed point, so the
+// forces do not.
+constexpr int kJposBlocks = 1024;   // workgroups of the super-cluster view's row pass
+
+struct FinishArgs {
+    int nregions, parts, per_item, pad0;   // no padding: job tables are compared byte by byte
+    const int *part_count, *part_start;
+    int *part_istart;
+    long cap_items, cap_rows;
+    int *totals, *flags;
+    int *jcount, *joff, *jstart;   // counters and offsets [set][jstride], first rows
+    int njc, nsets, jstride, pad1;
+    int4 *items;
     const nb_jentry *entries;
-    const int *jstart;   // first row of each j-cluster
-    int *jrank;          // rank in, row out
+    int *jrank;
 };
 
-// one wavefront per work item (a grid-stride loop), one lane per entry (items hold at most 64)
-__device__ inline void jpos_body(const JPosArgs &a, int blk, int nblk) {
-    const int lane = threadIdx.x & 63;
-    const int total = a.totals[2];
-    for (int t = blk * 4 + (threadIdx.x >> 6); t < total; t += nblk * 4) {
-        const int4 it = a.items[t];
-        const int e = it.y + lane;
-        if (e < it.z) a.jrank[e] += a.jstart[a.entries[e].cj];
+// The counters of four consecutive j-clusters from i on, summed over the sets; with CLEAR the counters are zeroed
+// and each set's offset within its j-cluster is written.
+template <bool CLEAR>
+__device__ inline int4 j_counts(const FinishArgs &a, int i) {
+    int n[mxn::kRankSets][4], sum[4] = {0, 0, 0, 0};
+    const bool whole = i + 4 <= a.njc && (a.nsets == 1 || (a.jstride & 3) == 0);   // the buffers are 16-byte aligned
+#pragma unroll
+    for (int s = 0; s < mxn::kRankSets; ++s) {   // every load in flight before the first store
+        const int *c = a.jcount + (long)s * a.jstride + i;
+        if (whole && s < a.nsets) {
+            const int4 x = *reinterpret_cast<const int4 *>(c);
+            n[s][0] = x.x; n[s][1] = x.y; n[s][2] = x.z; n[s][3] = x.w;
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) n[s][u] = s < a.nsets && i + u < a.njc ? c[u] : 0;
+        }
     }
+#pragma unroll
+    for (int s = 0; s < mxn::kRankSets; ++s) {
+        const long at = (long)s * a.jstride + i;
+        if (CLEAR && s < a.nsets) {
+            if (whole) {
+                *reinterpret_cast<int4 *>(a.jcount + at) = make_int4(0, 0, 0, 0);
+                if (a.joff) *reinterpret_cast<int4 *>(a.joff + at) = make_int4(sum[0], sum[1], sum[2], sum[3]);
+            } else {
+                for (int u = 0; u < 4 && i + u < a.njc; ++u) {
+                    a.jcount[at + u] = 0;
+                    if (a.joff) a.joff[at + u] = sum[u];
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) sum[u] += n[s][u];
+    }
+    return make_int4(sum[0], sum[1], sum[2], sum[3]);
 }
 
-constexpr int kJposBlocks = 1024;   // workgroups of the position pass (per replica in a batch: 256)
+// Exclusive scan of the entry counts of one tile's j-clusters into first rows, after the rows of the tiles before
+// it (carry; ends as those of the tiles up to it).
+constexpr int kTileJ = 4096;   // four per thread
+__device__ inline void j_tile(const FinishArgs &a, int base, int *carry) {
+    __shared__ int ws[16];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, i = base + t * 4;
+    const int4 v = j_counts<true>(a, i);
+    const int mine = (v.x + v.y) + (v.z + v.w);
+    const int incl = lane_scan(mine);
+    if (lane == 63) ws[w] = incl;
+    __syncthreads();
+    if (t < 64) {
+        const int x = lane_scan(t < 16 ? ws[t] : 0);
+        if (t < 16) ws[t] = x;
+    }
+    __syncthreads();
+    const int run = *carry + incl - mine + (w > 0 ? ws[w - 1] : 0);
+    if (i < a.njc) a.jstart[i] = run;
+    if (i + 1 < a.njc) a.jstart[i + 1] = run + v.x;
+    if (i + 2 < a.njc) a.jstart[i + 2] = run + v.x + v.y;
+    if (i + 3 < a.njc) a.jstart[i + 3] = run + v.x + v.y + v.z;
+    *carry += ws[15];
+    __syncthreads();   // ws reused by the next tile
+    if (t == 0 && base + kTileJ >= a.njc) a.jstart[a.njc] = *carry;
+}
 
+__device__ inline void j_scan(const FinishArgs &a) {
+    int carry = 0;
+    for (int base = 0; base < a.njc; base += kTileJ) j_tile(a, base, &carry);
+}
 
 // After a fill (or prune) pass, two independent workgroups of 1024 threads: the first scans the regions'
 // entry counts into item offsets and sets the usable item count (finalize_body, by the thread that wrote
-// the totals), the second scans the j-cluster counters into each j-cluster's first row and clears them
-// for the next build: one launch instead of three.  The items themselves are written by k_items.
-__global__ __launch_bounds__(1024) void k_finish(int nregions, int per_item, const int *part_count,
-                                                 int *part_istart, long cap_items, long cap_rows, int *totals,
-                                                 int *flags, int *jcount, int *jstart, int njc) {
-    if (blockIdx.x == 0) {
-        mxn::scan_body(part_count, part_istart, nregions, 2, per_item, totals + 1, totals);
-        finalize_body(totals, cap_items, cap_rows, flags);
+// the totals), the second scans the j-cluster counters.
+__device__ inline void finish_body(const FinishArgs &a, int which) {
+    if (which == 0) {
+        mxn::scan_body(a.part_count, a.part_istart, a.nregions, 2, a.per_item, a.totals + 1, a.totals);
+        finalize_body(a.totals, a.cap_items, a.cap_rows, a.flags);
     } else {
-        mxn::scan_body(jcount, jstart, njc, 0, 1, nullptr, nullptr, jcount);
+        j_scan(a);
     }
 }
+__global__ __launch_bounds__(1024) void k_finish(FinishArgs a) { finish_body(a, blockIdx.x); }
+
+// The same for long lists in two launches of one workgroup per tile: first the tiles' sums, then each tile's
+// scan from the sum of the tiles before it (one workgroup takes 123 us for the 3 million atom list's 380 000
+// regions and as many j-clusters).
+constexpr int kTileRegions = 8192;   // by 1024 threads
+__device__ inline int region_tiles(const FinishArgs &a) { return (a.nregions + kTileRegions - 1) / kTileRegions; }
+
+// sums over the workgroup's 1024 threads
+__device__ inline int2 block_sum2(int x, int y) {
+    __shared__ int2 red[16];
+    const int t = threadIdx.x;
+    x = __builtin_amdgcn_readlane(lane_scan(x), 63);
+    y = __builtin_amdgcn_readlane(lane_scan(y), 63);
+    if ((t & 63) == 0) red[t >> 6] = make_int2(x, y);
+    __syncthreads();
+    int2 s = make_int2(0, 0);
+    for (int k = 0; k < 16; ++k) {
+        s.x += red[k].x;
+        s.y += red[k].y;
+    }
+    __syncthreads();
+    return s;
+}
+
+__global__ __launch_bounds__(1024) void k_finish_sums(FinishArgs a, int2 *sums) {
+    const int tr = region_tiles(a), b = blockIdx.x, t = threadIdx.x;
+    int x = 0, y = 0;
+    if (b < tr) {   // (items, entries) of the tile's regions
+        for (int i = b * kTileRegions + t; i < min(a.nregions, (b + 1) * kTileRegions); i += 1024) {
+            const int c = a.part_count[i];
+            x += (c + a.per_item - 1) / a.per_item;
+            y += c;
+        }
+    } else {
+        const int4 v = j_counts<false>(a, (b - tr) * kTileJ + t * 4);
+        x = (v.x + v.y) + (v.z + v.w);
+    }
+    const int2 v = block_sum2(x, y);
+    if (t == 0) sums[b] = v;
+}
+
+__global__ __launch_bounds__(1024) void k_finish_tiles(FinishArgs a, const int2 *sums) {
+    const int tr = region_tiles(a), b = blockIdx.x, t = threadIdx.x;
+    const int first = b < tr ? 0 : tr;
+    int x = 0, y = 0;
+    for (int k = first + t; k < b; k += 1024) {
+        x += sums[k].x;
+        y += sums[k].y;
+    }
+    const int2 before = block_sum2(x, y);
+    if (b >= tr) {
+        int carry = before.x;
+        j_tile(a, (b - tr) * kTileJ, &carry);
+        return;
+    }
+    const int base = b * kTileRegions, n = min(kTileRegions, a.nregions - base);
+    mxn::scan_body(a.part_count + base, a.part_istart + base, n, 2, a.per_item, nullptr, nullptr, before.x,
+                   b == tr - 1);
+    if (b == tr - 1 && t == 0) {
+        a.totals[1] = before.x + sums[b].x;
+        a.totals[0] = before.y + sums[b].y;
+        finalize_body(a.totals, a.cap_items, a.cap_rows, a.flags);
+    }
+}
+
+// After the scans (and the distance sort, if any): one wavefront per region writes the region's work items
+// and turns each of its entries' rank into the entry's row (its j-cluster's first row, the offset of the set the
+// region's workgroup counted in, and the rank), for a usable list.
+__device__ inline void items_rows_body(const FinishArgs &a, int blk) {
+    const int g = __builtin_amdgcn_readfirstlane(blk * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    if (g >= a.nregions) return;
+    const int start = a.part_start[g], resv = a.part_start[g + 1] - start;
+    const int cnt = min(a.part_count[g], resv), ip = a.part_istart[g];
+    const int nit = (cnt + a.per_item - 1) / a.per_item;
+    for (int k = lane; k < nit; k += 64) {
+        if ((long)ip + k >= a.cap_items) break;   // overflow: latched by finalize_body
+        const int js = start + k * a.per_item;
+        a.items[ip + k] = make_int4(g / a.parts, js, min(js + a.per_item, start + cnt), 0);
+    }
+    if (a.totals[2] == 0) return;   // no usable items (or no entries): the rows are never read
+    const int *off = a.joff + (long)rank_set(blk) * a.jstride;
+    for (int e = start + lane; e < start + cnt; e += 64) {
+        const int cj = a.entries[e].cj;
+        a.jrank[e] += a.jstart[cj] + off[cj];
+    }
+}
+__global__ __launch_bounds__(256) void k_items_rows(FinishArgs a) { items_rows_body(a, blockIdx.x); }
 
 // Item offsets of full-length items over unchanged regions; an overflowed list (items, none usable) stays unusable.
 __global__ __launch_bounds__(1024) void k_full_items(int nregions, int per_item, const int *part_count,
@@ -536,27 +692,6 @@ __global__ __launch_bounds__(1024) void k_full_items(int nregions, int per_item,
 __global__ void k_items(int nparts_total, int parts, int per_item, const int *part_count, const int *part_start,
                         const int *part_istart, long cap_items, int4 *items) {
     items_body(nparts_total, parts, per_item, part_count, part_start, part_istart, cap_items, items, blockIdx.x);
-}
-
-// After k_finish (and the distance sort, if any): one wavefront per region writes the region's work items
-// and turns each of its entries' rank into the entry's row (its j-cluster's first row plus the rank), for
-// a usable list (in one launch: the items need not be read back to find the entries).
-__global__ __launch_bounds__(256) void k_items_rows(int nregions, int parts, int per_item, const int *part_count,
-                                                    const int *part_start, const int *part_istart, long cap_items,
-                                                    int4 *items, const int *totals, const nb_jentry *entries,
-                                                    const int *jstart, int *jrank) {
-    const int g = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (g >= nregions) return;
-    const int start = part_start[g], resv = part_start[g + 1] - start;
-    const int cnt = min(part_count[g], resv), ip = part_istart[g];
-    const int nit = (cnt + per_item - 1) / per_item;
-    for (int k = lane; k < nit; k += 64) {
-        if ((long)ip + k >= cap_items) break;   // overflow: latched by finalize_body
-        const int js = start + k * per_item;
-        items[ip + k] = make_int4(g / parts, js, min(js + per_item, start + cnt), 0);
-    }
-    if (totals[2] == 0) return;   // no usable items (or no entries): the rows are never read
-    for (int e = start + lane; e < start + cnt; e += 64) jrank[e] += jstart[entries[e].cj];
 }
 
 // --------------------------------------------------------------------------
@@ -582,7 +717,7 @@ struct PruneArgs {
     int *jcount, *jrank;
     int *region_overflow;
     float Lx, Ly, Lz, r2;
-    int nregions, parts;
+    int nregions, parts, jstride;
 };
 
 // Lane = (entry, j-particle), 64/N entries a step: an entry's particles are one coalesced 16 N-byte run (one lane per
@@ -664,7 +799,7 @@ __global__ __launch_bounds__(256) void k_prune(PruneArgs a) {
         if ((keep >> lane) & 1ull) {
             const int pos = start + cnt + __popcll(keep & ((1ull << lane) - 1ull));
             a.out[pos] = en;
-            a.jrank[pos] = atomicAdd(a.jcount + en.cj, 1);
+            a.jrank[pos] = atomicAdd(a.jcount + rank_set(blockIdx.x) * a.jstride + en.cj, 1);
         }
         cnt += __popcll(keep);
     }
@@ -811,15 +946,10 @@ __global__ __launch_bounds__(256) void k_sci_rows(const int *totals, const int4 
 
 struct ListJob {
     SearchArgs a;
-    JPosArgs jp;
-    int nregions, per_item;
-    int *part_count, *part_start, *part_istart, *totals;
-    int4 *items;
-    long cap_items, cap_rows;
-    int *flags;
+    FinishArgs f;
 };
 
-enum { LS_SEARCH, LS_ITEMS, LS_JPOS, LS_NSTAGES };
+enum { LS_SEARCH, LS_NSTAGES };   // one workgroup per four regions: the search and the last pass
 
 __device__ inline int job_of(const int *off, int n, int b) {
     int lo = 0, hi = n - 1;   // last r with off[r] <= b
@@ -837,23 +967,12 @@ __global__ __launch_bounds__(256) void kb_search(const ListJob *J, const int *of
     search_body<M, N, true>(to_global(J[r].a), blockIdx.x - off[r]);
 }
 
-__global__ void kb_items(const ListJob *J, const int *off, int n) {
+__global__ __launch_bounds__(1024) void kb_finish(const ListJob *J) { finish_body(J[blockIdx.x / 2].f, blockIdx.x & 1); }
+
+__global__ __launch_bounds__(256) void kb_items_rows(const ListJob *J, const int *off, int n) {
     const int r = job_of(off, n, blockIdx.x);
-    const ListJob &j = J[r];
-    items_body(j.nregions, j.a.parts, j.per_item, j.part_count, j.part_start, j.part_istart, j.cap_items, j.items,
-               blockIdx.x - off[r]);
+    items_rows_body(J[r].f, blockIdx.x - off[r]);
 }
-
-__global__ void kb_finalize(const ListJob *J) {
-    const ListJob &j = J[blockIdx.x];
-    finalize_body(j.totals, j.cap_items, j.cap_rows, j.flags);
-}
-
-__global__ __launch_bounds__(256) void kb_jpos(const ListJob *J, const int *off, int n) {
-    const int r = job_of(off, n, blockIdx.x);
-    jpos_body(J[r].jp, blockIdx.x - off[r], off[r + 1] - off[r]);
-}
-
 
 template <int M, int N>
 void run(nb_list *l, SearchArgs &a, bool fill, int nblocks, hipStream_t st) {
@@ -893,88 +1012,88 @@ static SearchArgs make_search(const nb_list *l, const int *excl_off, const int *
     a.part_start = (const int *)l->part_start.p;
     a.region_overflow = (int *)l->totals.p + 3;
     a.nci_cap = g->slots_cap / g->m;
+    a.jstride = rank_stride(g->slots_cap / g->nn);
     return a;
 }
 
 
-static JPosArgs make_jpos(const nb_list *l) {
-    JPosArgs v{};
-    v.totals = (const int *)l->totals.p;
-    v.items = (const int4 *)l->items.p;
-    v.entries = (const nb_jentry *)l->entries.p;
-    v.jstart = (const int *)l->jstart.p;
-    v.jrank = (int *)l->jrank.p;
-    return v;
+static FinishArgs make_finish(const nb_list *l, int nregions, int parts) {
+    const nb_grid *g = l->grid;
+    FinishArgs f{};
+    f.nregions = nregions;
+    f.parts = parts;
+    f.per_item = l->per_item;
+    f.part_count = (const int *)l->part_count.p;
+    f.part_start = (const int *)l->part_start.p;
+    f.part_istart = (int *)l->part_istart.p;
+    f.cap_items = l->cap_items;
+    f.cap_rows = l->cap_rows;
+    f.totals = (int *)l->totals.p;
+    f.flags = l->ctx->d_flags;
+    f.jcount = (int *)l->jcount.p;
+    f.joff = (int *)l->joff.p;
+    f.jstart = (int *)l->jstart.p;
+    f.njc = g->slots_cap / g->nn;
+    f.nsets = kRankSets;
+    f.jstride = rank_stride(f.njc);
+    f.items = (int4 *)l->items.p;
+    f.entries = (const nb_jentry *)l->entries.p;
+    f.jrank = (int *)l->jrank.p;
+    return f;
 }
 
-// item offsets per region (totals[0] = entries, totals[1] = items) and the work items
-// usable count and j-cluster first rows of a list after its fill or prune pass
-static void finish_list(nb_list *l, int nregions, hipStream_t st) {
-    const nb_grid *g = l->grid;
-    k_finish<<<2, 1024, 0, st>>>(nregions, l->per_item, (const int *)l->part_count.p,
-                                 (int *)l->part_istart.p, l->cap_items, l->cap_rows, (int *)l->totals.p,
-                                 l->ctx->d_flags, (int *)l->jcount.p, (int *)l->jstart.p, g->slots_cap / g->nn);
+// counters, offsets and tile sums of a list with njc j-clusters; the sums come after the offsets
+static size_t joff_bytes(long njc, long nregions) {
+    const long tiles = (nregions + kTileRegions - 1) / kTileRegions + (njc + kTileJ - 1) / kTileJ;
+    return (size_t)kRankSets * rank_stride(njc) * 4 + (size_t)tiles * sizeof(int2);
+}
+
+// item offsets per region (totals[0] = entries, totals[1] = items), usable count and j-cluster first rows of a
+// list after its fill or prune pass
+static void finish_list(const FinishArgs &f, hipStream_t st) {
+    const int tr = (f.nregions + kTileRegions - 1) / kTileRegions, tj = (f.njc + kTileJ - 1) / kTileJ;
+    if (tr <= kOneGroupTiles / 2 && tj <= kOneGroupTiles) {
+        k_finish<<<2, 1024, 0, st>>>(f);
+    } else {
+        int2 *sums = (int2 *)(f.joff + (long)kRankSets * f.jstride);
+        k_finish_sums<<<tr + tj, 1024, 0, st>>>(f, sums);
+        k_finish_tiles<<<tr + tj, 1024, 0, st>>>(f, sums);
+    }
 }
 // work items and each usable entry's row (after finish_list, and after the distance sort)
-static void finish_rows(nb_list *l, int nregions, int parts, hipStream_t st) {
-    k_items_rows<<<(nregions + 3) / 4, 256, 0, st>>>(nregions, parts, l->per_item,
-                                                     (const int *)l->part_count.p, (const int *)l->part_start.p,
-                                                     (const int *)l->part_istart.p, l->cap_items,
-                                                     (int4 *)l->items.p, (const int *)l->totals.p,
-                                                     (const nb_jentry *)l->entries.p, (const int *)l->jstart.p,
-                                                     (int *)l->jrank.p);
-}
+static void finish_rows(const FinishArgs &f, hipStream_t st) { k_items_rows<<<(f.nregions + 3) / 4, 256, 0, st>>>(f); }
 
 size_t list_job_size() { return sizeof(ListJob); }
 int list_job_stages() { return LS_NSTAGES; }
 
 // The list must have been sized by a synchronous build for its grid's capacity.
-void fill_list_job(void *out, nb_list *l, const int *excl_off, const int *excl_idx, ScanJob *scan,
-                   ScanJob *jscan) {
+void fill_list_job(void *out, nb_list *l, const int *excl_off, const int *excl_idx) {
     ListJob j{};
     j.a = make_search(l, excl_off, excl_idx);
     j.a.jcount = (int *)l->jcount.p;
     j.a.jrank = (int *)l->jrank.p;
-    j.jp = make_jpos(l);
     j.a.parts = l->resv_parts;
     j.a.entries = (nb_jentry *)l->entries.p;
     j.a.keys = nullptr;
-    j.nregions = l->resv_nci * l->resv_parts;
-    j.per_item = l->per_item;
-    j.part_count = (int *)l->part_count.p;
-    j.part_start = (int *)l->part_start.p;
-    j.part_istart = (int *)l->part_istart.p;
-    j.totals = (int *)l->totals.p;
-    j.items = (int4 *)l->items.p;
-    j.cap_items = l->cap_items;
-    j.cap_rows = l->cap_rows;
-    j.flags = l->ctx->d_flags;
+    j.f = make_finish(l, l->resv_nci * l->resv_parts, l->resv_parts);
     std::memcpy(out, &j, sizeof j);
-    *scan = ScanJob{j.part_count, j.part_istart, j.nregions, 2, j.per_item, j.totals + 1, j.totals, nullptr};
-    int *jc = (int *)l->jcount.p;
-    *jscan = ScanJob{jc, (int *)l->jstart.p, l->grid->slots_cap / l->grid->nn, 0, 1, nullptr, nullptr, jc};
 }
 
 void list_job_blocks(const nb_list *l, int *blocks_per_stage) {
     const long nreg = (long)l->resv_nci * l->resv_parts;
     blocks_per_stage[LS_SEARCH] = (int)((nreg + 3) / 4);
-    blocks_per_stage[LS_ITEMS] = (int)((nreg + 255) / 256);
-    blocks_per_stage[LS_JPOS] = (int)std::max(1L, std::min<long>((l->cap_items + 3) / 4, kJposBlocks / 4));
 }
 
-int launch_pairlist_batch(hipStream_t st, int m, int nn, const void *jobs, const int *off, int n_rep, const int *total,
-                          const ScanJob *scans) {
+int launch_pairlist_batch(hipStream_t st, int m, int nn, const void *jobs, const int *off, int n_rep,
+                          const int *total) {
     const ListJob *J = (const ListJob *)jobs;
-    const int stride = n_rep + 1;
-    if (m == 4 && nn == 4) kb_search<4, 4><<<total[LS_SEARCH], 256, 0, st>>>(J, off + LS_SEARCH * stride, n_rep);
-    else if (m == 4 && nn == 8) kb_search<4, 8><<<total[LS_SEARCH], 256, 0, st>>>(J, off + LS_SEARCH * stride, n_rep);
-    else if (m == 8 && nn == 4) kb_search<8, 4><<<total[LS_SEARCH], 256, 0, st>>>(J, off + LS_SEARCH * stride, n_rep);
-    else kb_search<8, 8><<<total[LS_SEARCH], 256, 0, st>>>(J, off + LS_SEARCH * stride, n_rep);
-    launch_scan_batch(scans, n_rep, st);
-    kb_items<<<total[LS_ITEMS], 256, 0, st>>>(J, off + LS_ITEMS * stride, n_rep);
-    kb_finalize<<<n_rep, 64, 0, st>>>(J);
-    launch_scan_batch(scans + n_rep, n_rep, st);
-    kb_jpos<<<total[LS_JPOS], 256, 0, st>>>(J, off + LS_JPOS * stride, n_rep);
+    const int nb = total[LS_SEARCH];
+    if (m == 4 && nn == 4) kb_search<4, 4><<<nb, 256, 0, st>>>(J, off, n_rep);
+    else if (m == 4 && nn == 8) kb_search<4, 8><<<nb, 256, 0, st>>>(J, off, n_rep);
+    else if (m == 8 && nn == 4) kb_search<8, 4><<<nb, 256, 0, st>>>(J, off, n_rep);
+    else kb_search<8, 8><<<nb, 256, 0, st>>>(J, off, n_rep);
+    kb_finish<<<2 * n_rep, 1024, 0, st>>>(J);
+    kb_items_rows<<<nb, 256, 0, st>>>(J, off, n_rep);
     MXN_HIP(hipGetLastError());
     return NB_OK;
 }
@@ -1013,10 +1132,9 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
         else if (g->m == 4 && g->nn == 8) run<4, 8>(l, a, false, nblocks, st);
         else if (g->m == 8 && g->nn == 4) run<8, 4>(l, a, false, nblocks, st);
         else run<8, 8>(l, a, false, nblocks, st);
-        k_max_count<<<1, 1024, 0, st>>>((const int *)l->part_count.p, nregions, item_entries(g->nn),
-                                         (int *)l->totals.p);
-        MXN_HIP(hipMemcpyAsync(ctx->h_pinned, l->totals.p, 6 * sizeof(int), hipMemcpyDeviceToHost, st));
-        MXN_HIP(hipMemsetAsync((int *)l->totals.p + 3, 0, sizeof(int), st));
+        // the sums go straight to pinned host memory
+        k_max_count<<<1, 1024, 0, st>>>((const int *)l->part_count.p, nregions, item_entries(g->nn), ctx->h_pinned);
+        MXN_HIP(hipGetLastError());
         MXN_HIP(hipStreamSynchronize(st));
         const long mx = ctx->h_pinned[0];
         const long size = mx + mx / 4 + 8;
@@ -1048,7 +1166,9 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
         }
         // j-cluster view and force-call buffers for this capacity; the counters start cleared
         const long njc = g->slots_cap / g->nn;
-        int rc = ensure(l->ctx, l->jcount, (size_t)(njc + 1) * 4);
+        const long nsc = (long)kRankSets * rank_stride(njc);
+        int rc = ensure(l->ctx, l->jcount, (size_t)nsc * 4);
+        rc = rc ? rc : ensure(l->ctx, l->joff, joff_bytes(njc, nregions));
         rc = rc ? rc : ensure(l->ctx, l->jstart, (size_t)(njc + 1) * 4);
         rc = rc ? rc : ensure(l->ctx, l->jrank, (size_t)l->cap_entries * 4);
         // j-force rows (one per entry, 12 N bytes): the synchronous build's entries plus a quarter, not the regions'
@@ -1062,8 +1182,8 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
         }
         rc = rc ? rc : ensure(l->ctx, l->fi, (size_t)l->cap_items * g->m * 16);
         if (rc) return rc;
-        MXN_HIP(hipMemsetAsync(l->jcount.p, 0, (size_t)(njc + 1) * 4, st));
-        k_region_starts<<<(nregions + 256) / 256, 256, 0, st>>>(nregions, (int)size, (int *)l->part_start.p);
+        k_reserve<<<(nregions + 256) / 256, 256, 0, st>>>(nregions, (int)size, (int *)l->part_start.p, (int)nsc,
+                                                          (int *)l->jcount.p, (int *)l->totals.p);
         l->resv_parts = parts;
         l->resv_nci = nci_cap;
         l->last_entries = ce;
@@ -1088,13 +1208,14 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
     else if (g->m == 4 && g->nn == 8) run<4, 8>(l, a, true, nblocks, st);
     else if (g->m == 8 && g->nn == 4) run<8, 4>(l, a, true, nblocks, st);
     else run<8, 8>(l, a, true, nblocks, st);
-    finish_list(l, nregions, st);
+    const FinishArgs f = make_finish(l, nregions, parts);
+    finish_list(f, st);
     if (by_distance)
         k_sort_entries<<<nregions, 64, 0, st>>>((const int *)l->part_start.p, (const int *)l->part_count.p,
                                                 (const nb_jentry *)l->entries_canon.p, (const float *)l->keys.p,
                                                 (nb_jentry *)l->entries.p, (const int *)l->jrank_canon.p,
                                                 (int *)l->jrank.p);
-    finish_rows(l, nregions, parts, st);
+    finish_rows(f, st);
     l->sci_valid = false;
     MXN_HIP(hipGetLastError());
     return NB_OK;
@@ -1170,8 +1291,21 @@ int launch_sci_view(const nb_list *l, int S, int per_item) {
     int *tot = (int *)l->sci_totals.p;
     k_sci_view<<<ngroups, 256, 0, st>>>(a);
     // rows: a super-cluster entry stands for one or more of the list's entries, which fit l's rows
-    k_finish<<<2, 1024, 0, st>>>(ngroups, per_item, a.count, (int *)l->sci_istart.p, cap_items, l->cap_rows, tot,
-                                 l->ctx->d_flags, a.jcount, (int *)l->sci_jstart.p, (int)njc);
+    FinishArgs f{};
+    f.nregions = ngroups;
+    f.per_item = per_item;
+    f.part_count = a.count;
+    f.part_istart = (int *)l->sci_istart.p;
+    f.cap_items = cap_items;
+    f.cap_rows = l->cap_rows;
+    f.totals = tot;
+    f.flags = l->ctx->d_flags;
+    f.jcount = a.jcount;
+    f.jstart = (int *)l->sci_jstart.p;
+    f.njc = (int)njc;
+    f.nsets = 1;
+    f.jstride = (int)njc;
+    k_finish<<<2, 1024, 0, st>>>(f);
     k_items<<<(ngroups + 255) / 256, 256, 0, st>>>(ngroups, 1, per_item, a.count, a.base,
                                                   (const int *)l->sci_istart.p, cap_items, (int4 *)l->sci_items.p);
     const int nb = (int)std::max<long>(1, std::min<long>((cap_items + 3) / 4, kJposBlocks));
@@ -1199,15 +1333,17 @@ int launch_prune(nb_list *in, const nb_list *outer, float r) {
     rc = rc ? rc : ensure(in->ctx, in->totals, 32);
     rc = rc ? rc : ensure(in->ctx, in->entries, (size_t)outer->cap_entries * sizeof(nb_jentry));
     rc = rc ? rc : ensure(in->ctx, in->items, (size_t)outer->cap_items * sizeof(int4));
-    rc = rc ? rc : ensure(in->ctx, in->jcount, (size_t)(njc + 1) * 4);
+    const long nsc = (long)kRankSets * rank_stride(njc);
+    rc = rc ? rc : ensure(in->ctx, in->jcount, (size_t)nsc * 4);
+    rc = rc ? rc : ensure(in->ctx, in->joff, joff_bytes(njc, nregions));
     rc = rc ? rc : ensure(in->ctx, in->jstart, (size_t)(njc + 1) * 4);
     rc = rc ? rc : ensure(in->ctx, in->jrank, (size_t)outer->cap_entries * 4);
     rc = rc ? rc : ensure(in->ctx, in->fj, (size_t)outer->cap_rows * g->nn * 12);
     rc = rc ? rc : ensure(in->ctx, in->fi, (size_t)outer->cap_items * g->m * 16);
     if (rc) return rc;
     if (in->jcount.p != old_jc || in->resv_nci != outer->resv_nci)
-        MXN_HIP(hipMemsetAsync(in->jcount.p, 0, (size_t)(njc + 1) * 4, st));
-    if (in->totals.p != old_tot) MXN_HIP(hipMemsetAsync(in->totals.p, 0, 16, st));
+        MXN_HIP(hipMemsetAsync(in->jcount.p, 0, (size_t)nsc * 4, st));
+    if (in->totals.p != old_tot) MXN_HIP(hipMemsetAsync(in->totals.p, 0, 32, st));
     in->grid = g;
     in->grid_generation = outer->grid_generation;
     in->rlist = r;
@@ -1243,13 +1379,15 @@ int launch_prune(nb_list *in, const nb_list *outer, float r) {
     a.r2 = r2;
     a.nregions = nregions;
     a.parts = outer->resv_parts;
+    a.jstride = rank_stride(njc);
     const int nb = (nregions + 3) / 4;
     if (g->m == 4 && g->nn == 4) k_prune<4, 4><<<nb, 256, 0, st>>>(a);
     else if (g->m == 4 && g->nn == 8) k_prune<4, 8><<<nb, 256, 0, st>>>(a);
     else if (g->m == 8 && g->nn == 4) k_prune<8, 4><<<nb, 256, 0, st>>>(a);
     else k_prune<8, 8><<<nb, 256, 0, st>>>(a);
-    finish_list(in, nregions, st);
-    finish_rows(in, nregions, outer->resv_parts, st);
+    const FinishArgs f = make_finish(in, nregions, outer->resv_parts);
+    finish_list(f, st);
+    finish_rows(f, st);
     MXN_HIP(hipGetLastError());
     return NB_OK;
 }

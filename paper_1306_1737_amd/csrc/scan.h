@@ -10,8 +10,7 @@ namespace mxn {
 
 // Exclusive scan on one workgroup of 1024 threads; mode 0: values as is,
 // 1: rounded up to a multiple of p, 2: ceil(v/p).  raw_total (optional)
-// receives the sum of the untransformed values; clear (optional, the input
-// array itself) is zeroed once read.  Tiles of 8192 values: thread t reads
+// receives the sum of the untransformed values.  Tiles of 8192 values: thread t reads
 // and writes the eight consecutive values t*8 .. t*8+7 of the tile straight
 // from and to memory (two 16-byte accesses when the arrays are 16-byte
 // aligned, which makes each wavefront access one contiguous 2 KB run), the
@@ -58,12 +57,12 @@ __device__ inline void block_scan2(int &s, int &r, int *ws, int *wr) {
 }
 
 __device__ inline void scan_body(const int *in, int *out, int n, int mode, int p, int *total, int *raw_total,
-                                 int *clear = nullptr) {
+                                 int carry = 0, bool last = true) {
     __shared__ int ws[16], wr[16];
     const int t = threadIdx.x;
     auto tr = [&](int v) { return mode == 0 ? v : (mode == 1 ? (v + p - 1) / p * p : (v + p - 1) / p); };
     const bool vec = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
-    int carry = 0, rcarry = 0;
+    int rcarry = 0;
     for (int base = 0; base < n; base += kScanTile) {
         const int i0 = base + t * kScanPer;
         const bool whole = vec && i0 + kScanPer <= n;
@@ -76,16 +75,6 @@ __device__ inline void scan_body(const int *in, int *out, int n, int mode, int p
         } else {
 #pragma unroll
             for (int u = 0; u < kScanPer; ++u) v[u] = i0 + u < n ? in[i0 + u] : 0;
-        }
-        if (clear) {
-            if (whole) {
-                *reinterpret_cast<int4 *>(clear + i0) = make_int4(0, 0, 0, 0);
-                *reinterpret_cast<int4 *>(clear + i0 + 4) = make_int4(0, 0, 0, 0);
-            } else {
-#pragma unroll
-                for (int u = 0; u < kScanPer; ++u)
-                    if (i0 + u < n) clear[i0 + u] = 0;
-            }
         }
         int s = 0, r = 0;
 #pragma unroll
@@ -121,7 +110,7 @@ __device__ inline void scan_body(const int *in, int *out, int n, int mode, int p
         __syncthreads();   // ws reused by the next tile
     }
     if (t == 0) {
-        out[n] = carry;
+        if (last) out[n] = carry;
         if (total) *total = carry;
         if (raw_total) *raw_total = rcarry;
     }
