@@ -358,6 +358,35 @@ __device__ inline float wave_sum8_t(const float (&v)[8], int lane) {
     return octet_sum(keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(send), 0x128, 0xf, 0xf, false)));
 }
 
+// Totals of v[0..7] with wave_sum_dpp's grouping (lane pairs, then aligned fours, ... halves: the virial is formed
+// from these FP32 sums, so their rounding is part of its result), two to a lane: t[k] is the total of
+// v[k + 2 (lane >= 32) + 4 (odd row)].  The four levels inside a row are taken by every value, the last two
+// transposed.
+__device__ inline void wave_sum8_rows(const float (&v)[8], float (&t)[2]) {
+    float x[8], g[4];
+    const auto step = [&](auto ctrl) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            x[k] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x[k]), ctrl.value, 0xf, 0xf, true));
+    };
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = v[k];
+    step(std::integral_constant<int, 0xB1>{});    // quad [1,0,3,2]
+    step(std::integral_constant<int, 0x4E>{});    // quad [2,3,0,1]
+    step(std::integral_constant<int, 0x141>{});   // half-row mirror: the other four of the eight
+    step(std::integral_constant<int, 0x140>{});   // row mirror: the other eight of the row
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {   // even rows keep x[k], odd rows x[k + 4]
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x[k]), __float_as_uint(x[k + 4]), false, false);
+        g[k] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {   // lanes 0-31 keep g[k], lanes 32-63 g[k + 2]
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(g[k]), __float_as_uint(g[k + 2]), false, false);
+        t[k] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+}
+
 // The same transposed totals of v[0..7] for FP64 sums (a virial's nine by eight separate sums and bpermutes took
 // about 160 instructions and 108 LDS operations an item).
 __device__ inline double item_sum8_t(const double (&v)[9], int lane) {
@@ -460,34 +489,48 @@ __device__ inline void force_item(const ForceArgs &a, const SysView &v, const fl
             vir[6] += (acc_t)(zj * fjx); vir[7] += (acc_t)(zj * fjy); vir[8] += (acc_t)(zj * fjz);
         }
     }
-    // i-forces: one reduction across the wavefront per work item
-    acc_t viri[9];
-#pragma unroll
-    for (int k = 0; k < 9; ++k) viri[k] = 0;
-    // transposed sums (octet o stores i-particle o) in the single-system kernel; the batched kernel keeps
-    // eight wavefront sums (the transposed form takes it to 75 registers and measured 2 % slower there)
-    if constexpr (M == 8 && !VIR && LM) {
+    // i-forces: one reduction across the wavefront per work item.  With the virial, x_i (x) F_i is added to one
+    // lane's share of its sums.
+    const auto add_i = [&](const float4 &p, float fx, float fy, float fz) {
+        vir[0] += (acc_t)p.x * (acc_t)fx; vir[1] += (acc_t)p.x * (acc_t)fy; vir[2] += (acc_t)p.x * (acc_t)fz;
+        vir[3] += (acc_t)p.y * (acc_t)fx; vir[4] += (acc_t)p.y * (acc_t)fy; vir[5] += (acc_t)p.y * (acc_t)fz;
+        vir[6] += (acc_t)p.z * (acc_t)fx; vir[7] += (acc_t)p.z * (acc_t)fy; vir[8] += (acc_t)p.z * (acc_t)fz;
+    };
+    if constexpr (M == 8 && VIR) {
+        // two i-particles to a row of lanes (eight sums for lane 63 and its 72 products one after the other: 121
+        // against 116 us a launch at 96 000 atoms)
+        const int i0 = 2 * (lane >> 5) + 4 * ((lane >> 4) & 1);
+        const int s0 = ci * M + i0;
+        const float4 p0 = OWN ? own_particle(a, s0) : ld(v.xs_now + s0);
+        const float4 p1 = OWN ? own_particle(a, s0 + 1) : ld(v.xs_now + s0 + 1);
+        float fx[2], fy[2], fz[2];
+        wave_sum8_rows(fix, fx);
+        wave_sum8_rows(fiy, fy);
+        wave_sum8_rows(fiz, fz);
+        if ((lane & 15) == 0) {
+            mxn::st(v.fi + (long)item * M + i0, make_float4(fx[0], fy[0], fz[0], 0.0f));
+            mxn::st(v.fi + (long)item * M + i0 + 1, make_float4(fx[1], fy[1], fz[1], 0.0f));
+            add_i(p0, fx[0], fy[0], fz[0]);
+            add_i(p1, fx[1], fy[1], fz[1]);
+        }
+    } else if constexpr (M == 8 && LM) {
+        // transposed sums (octet o stores i-particle o) in the single-system kernel; the batched kernel keeps
+        // eight wavefront sums (the transposed form takes it to 75 registers and measured 2 % slower there)
         const float fx = wave_sum8_t(fix, lane), fy = wave_sum8_t(fiy, lane), fz = wave_sum8_t(fiz, lane);
         if ((lane & 7) == 0) mxn::st(v.fi + (long)item * M + (lane >> 3), make_float4(fx, fy, fz, 0.0f));
     } else {
 #pragma unroll
-    for (int k = 0; k < M; ++k) {
-        const float fx = wave_sum_dpp(fix[k]), fy = wave_sum_dpp(fiy[k]), fz = wave_sum_dpp(fiz[k]);
-        if (lane == 63) {
-            mxn::st(v.fi + (long)item * M + k, make_float4(fx, fy, fz, 0.0f));
-            if (VIR) {
-                viri[0] += (acc_t)xi[k] * (acc_t)fx; viri[1] += (acc_t)xi[k] * (acc_t)fy; viri[2] += (acc_t)xi[k] * (acc_t)fz;
-                viri[3] += (acc_t)yi[k] * (acc_t)fx; viri[4] += (acc_t)yi[k] * (acc_t)fy; viri[5] += (acc_t)yi[k] * (acc_t)fz;
-                viri[6] += (acc_t)zi[k] * (acc_t)fx; viri[7] += (acc_t)zi[k] * (acc_t)fy; viri[8] += (acc_t)zi[k] * (acc_t)fz;
+        for (int k = 0; k < M; ++k) {
+            const float fx = wave_sum_dpp(fix[k]), fy = wave_sum_dpp(fiy[k]), fz = wave_sum_dpp(fiz[k]);
+            if (lane == 63) {
+                mxn::st(v.fi + (long)item * M + k, make_float4(fx, fy, fz, 0.0f));
+                if (VIR) add_i(make_float4(xi[k], yi[k], zi[k], 0.0f), fx, fy, fz);
             }
         }
-    }
     }
     // energies and virial of the item (virial slots are read only with the virial)
     const auto store = [&](int k, acc_t x) { v.partials[(size_t)k * v.pstride + v.pbase + item] = (double)x; };
     if (VIR) {
-#pragma unroll
-        for (int k = 0; k < 9; ++k) vir[k] += viri[k];   // zero but in lane 63
         if constexpr (ACC64) {
             const double tot = item_sum8_t(vir, lane), last = item_sum(vir[8]);
             if ((lane & 7) == 0) store(2 + (lane >> 3), tot);
