@@ -56,8 +56,7 @@ __device__ inline float wrap1(float x, float L, double il, int &k, bool &bad) {
 constexpr int kHistThreads = 1024;
 constexpr int kColsPerBlock = 4;   // columns per workgroup of the per-column prefix (one wavefront each)
 
-__device__ inline int wrap_column(const WrapArgs &a, int i) {
-    float4 p = a.xyzq[i];
+__device__ inline int wrap_column(const WrapArgs &a, int i, const float4 &p) {
     bool bad = !(isfinite(p.x) && isfinite(p.y) && isfinite(p.z) && isfinite(p.w));
     int kx, ky, kz;
     float wx = wrap1(p.x, a.Lx, a.ilx, kx, bad);
@@ -74,6 +73,8 @@ __device__ inline int wrap_column(const WrapArgs &a, int i) {
     a.atom_xw[i] = make_float4(wx, wy, wz, p.w);
     return col;
 }
+
+__device__ inline int wrap_column(const WrapArgs &a, int i) { return wrap_column(a, i, a.xyzq[i]); }
 
 // Kernel bodies take their workgroup index `blk` explicitly: the
 // single-system kernels pass blockIdx.x, the batched ones the index within
@@ -382,6 +383,42 @@ __global__ __launch_bounds__(1024) void k_col_scan(const int *col_count, int *co
 }
 
 
+// Small systems: wrap, column counts, column starts and buckets in one workgroup instead of four launches, which
+// are all launch and latency at this size (3000 atoms 7 us against 12 and the gaps between them; 12 000 atoms 16
+// against 15).
+constexpr int kOneGroupAtoms = 8192, kOneGroupColumns = 4096;
+__global__ __launch_bounds__(1024) void k_bin_small(WrapArgs a, int ncol, int cmax, int *col_start, int *nslots,
+                                                    float4 *sv, int *bucket) {
+    extern __shared__ int h[];
+    const int t = threadIdx.x;
+    shiftvec_body(sv, a.Lx, a.Ly, a.Lz);
+    for (int c = t; c < ncol; c += 1024) h[c] = 0;
+    __syncthreads();
+    for (int i0 = t; i0 < a.n; i0 += 4096) {   // four loads in flight
+        float4 p[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) p[u] = a.xyzq[min(i0 + u * 1024, a.n - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i0 + u * 1024 < a.n) atomicAdd(&h[wrap_column(a, i0 + u * 1024, p[u])], 1);
+    }
+    __syncthreads();
+    for (int c = t; c < ncol; c += 1024) a.col_count[c] = h[c];
+    __syncthreads();
+    scan_body(a.col_count, col_start, ncol, 1, cmax, nslots, nullptr);
+    __syncthreads();
+    for (int c = t; c < ncol; c += 1024) h[c] = col_start[c];
+    __syncthreads();
+    for (int i0 = t; i0 < a.n; i0 += 4096) {
+        int c[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c[u] = a.atom_col[min(i0 + u * 1024, a.n - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i0 + u * 1024 < a.n) bucket[atomicAdd(&h[c[u]], 1)] = i0 + u * 1024;
+    }
+}
+
 __global__ void k_fill_int(int *p, int n, int v) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -520,24 +557,29 @@ int launch_grid_sort(nb_grid *g, const float *xyzq, const int *type) {
     const bool lds_hist = ncol <= kMaxHistColumns;
     const int nhb = hist_blocks(n);
     const size_t hb = (size_t)ncol * sizeof(int);
-    if (lds_hist) {
-        k_wrap_hist<<<nhb, kHistThreads, hb, st>>>(w, ncol, nhb, (int *)g->col_hist.p);
-        k_col_prefix<<<blocks(ncol, kColsPerBlock), 256, 0, st>>>(ncol, nhb, (int *)g->col_hist.p,
-                                                                   (int *)g->col_count.p);
+    if (n <= kOneGroupAtoms && ncol <= kOneGroupColumns) {
+        k_bin_small<<<1, 1024, hb, st>>>(w, ncol, g->cmax, (int *)g->col_start.p, (int *)g->nslots.p,
+                                         (float4 *)g->shiftvec.p, (int *)g->bucket.p);
     } else {
-        k_fill_int<<<blocks(ncol, 256), 256, 0, st>>>((int *)g->col_count.p, ncol, 0);
-        k_wrap_count<<<blocks(n, 256), 256, 0, st>>>(w);
-    }
-    k_col_scan<<<1, 1024, 0, st>>>((const int *)g->col_count.p, (int *)g->col_start.p, ncol, g->cmax,
-                                   (int *)g->nslots.p, (float4 *)g->shiftvec.p, g->Lf[0], g->Lf[1], g->Lf[2]);
-    if (lds_hist) {
-        k_bucket_hist<<<nhb, kHistThreads, hb, st>>>(n, ncol, nhb, (const int *)g->atom_col.p,
-                                                     (const int *)g->col_start.p, (const int *)g->col_hist.p,
-                                                     (int *)g->bucket.p);
-    } else {
-        k_fill_int<<<blocks(ncol, 256), 256, 0, st>>>((int *)g->col_fill.p, ncol, 0);
-        k_bucket<<<blocks(n, 256), 256, 0, st>>>(n, (const int *)g->atom_col.p, (const int *)g->col_start.p,
-                                                 (int *)g->col_fill.p, (int *)g->bucket.p);
+        if (lds_hist) {
+            k_wrap_hist<<<nhb, kHistThreads, hb, st>>>(w, ncol, nhb, (int *)g->col_hist.p);
+            k_col_prefix<<<blocks(ncol, kColsPerBlock), 256, 0, st>>>(ncol, nhb, (int *)g->col_hist.p,
+                                                                       (int *)g->col_count.p);
+        } else {
+            k_fill_int<<<blocks(ncol, 256), 256, 0, st>>>((int *)g->col_count.p, ncol, 0);
+            k_wrap_count<<<blocks(n, 256), 256, 0, st>>>(w);
+        }
+        k_col_scan<<<1, 1024, 0, st>>>((const int *)g->col_count.p, (int *)g->col_start.p, ncol, g->cmax,
+                                       (int *)g->nslots.p, (float4 *)g->shiftvec.p, g->Lf[0], g->Lf[1], g->Lf[2]);
+        if (lds_hist) {
+            k_bucket_hist<<<nhb, kHistThreads, hb, st>>>(n, ncol, nhb, (const int *)g->atom_col.p,
+                                                         (const int *)g->col_start.p, (const int *)g->col_hist.p,
+                                                         (int *)g->bucket.p);
+        } else {
+            k_fill_int<<<blocks(ncol, 256), 256, 0, st>>>((int *)g->col_fill.p, ncol, 0);
+            k_bucket<<<blocks(n, 256), 256, 0, st>>>(n, (const int *)g->atom_col.p, (const int *)g->col_start.p,
+                                                     (int *)g->col_fill.p, (int *)g->bucket.p);
+        }
     }
     const SortArgs s = make_sort(g, type);
     k_col_sort<<<ncol, kSortThreads, 0, st>>>(s);
