@@ -92,6 +92,8 @@ struct ForceArgs {
     int own;          // no gather: the force kernel reads the caller's positions, the fold checks them
     int *flags;
     long pstride;     // partials layout: [kNAcc][pstride]
+    double *zero;     // values the gather clears
+    int nzero;
 };
 
 // A particle's position at the evaluated time moved by the periodic image its
@@ -115,6 +117,7 @@ __device__ inline float4 own_particle(const ForceArgs &a, int s) {
 
 __global__ void k_gather(ForceArgs a) {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    for (int k = s; k < a.nzero; k += gridDim.x * blockDim.x) a.zero[k] = 0.0;
     if (s >= *a.nslots) return;
     const int o = a.perm[s];
     if (o >= 0) {
@@ -1360,8 +1363,10 @@ int launch_batch_shape(const ForceArgs &a, const BatchArgs &b, unsigned flags, l
 
 namespace mxn {
 
-int launch_gather(nb_ctx *ctx, const nb_grid *g, const float *xyzq_now, int nt) {
+int launch_gather(nb_ctx *ctx, const nb_grid *g, const float *xyzq_now, int nt, double *zero, int nzero) {
     ForceArgs a{};
+    a.zero = zero;
+    a.nzero = nzero;
     a.type_s = (const int *)g->type_s.p;
     a.nt = nt;
     a.nslots = (const int *)g->nslots.p;

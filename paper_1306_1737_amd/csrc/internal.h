@@ -285,8 +285,9 @@ int launch_stats(nb_ctx *ctx, const nb_grid *g, const nb_list *l, const float *x
 // at the grid's gathered positions (xs_now)
 int launch_prune(nb_list *in, const nb_list *outer, float r);
 // coordinate gather into the grid's slot order; with nt > 0 it also latches
-// FLAG_TYPE for a particle whose LJ type is not below nt
-int launch_gather(nb_ctx *ctx, const nb_grid *g, const float *xyzq_now, int nt = 0);
+// FLAG_TYPE for a particle whose LJ type is not below nt; zero (optional): nzero values to clear
+int launch_gather(nb_ctx *ctx, const nb_grid *g, const float *xyzq_now, int nt = 0, double *zero = nullptr,
+                  int nzero = 0);
 // super-cluster view of an 8x8 list: i-clusters per super-cluster (0: none) and the build
 constexpr int kSciPerItem = 16;
 int sci_size(const nb_list *l, int want);

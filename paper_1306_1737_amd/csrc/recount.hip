@@ -16,14 +16,15 @@
 // The bins of interest are a few dozen addresses, and one FP64 atomic per
 // contributing lane on them bound the kernel (130 us for 12 000 atoms listed
 // to 1.5 nm, 20 us of it VALU issue).  Persistent workgroups therefore add
-// into an LDS histogram and flush it once: 37 us.
+// into an LDS histogram and flush it once: 37 us, and 35 with the passes that
+// hold no pair within the cut-off dropped before their thresholds.
 #include "ewald_fit.h"
 #include "internal.h"
 
 namespace {
 
 struct RecountArgs {
-    const int *perm, *type_s;
+    const int *type_s;   // -1 for dummy slots
     const float4 *xs, *xs_now;
     const float4 *bbi_lo, *bbi_hi, *bbj_lo, *bbj_hi;
     const int4 *items;
@@ -83,7 +84,7 @@ __global__ __launch_bounds__(64 * kRecountWaves) void k_recount(RecountArgs a) {
             qi[k] = pt.w * a.coulomb_f;
             const int t = a.type_s[ci * M + k];
             ti[k] = (t < 0 ? 0 : (t >= a.nt ? a.nt - 1 : t)) * a.nt;
-            ireal[k] = a.perm[ci * M + k] >= 0;
+            ireal[k] = t >= 0;
         }
         const float4 ilo = a.bbi_lo[ci], ihi = a.bbi_hi[ci];
         const int jb = lane % N, eo = lane / N;
@@ -94,7 +95,24 @@ __global__ __launch_bounds__(64 * kRecountWaves) void k_recount(RecountArgs a) {
             const int jslot = en.cj * N + jb;
             const float4 pj0 = a.xs[jslot], pjt = a.xs_now[jslot];
             const float4 sv = svec[en.shift];
-            const bool jreal = a.perm[jslot] >= 0;
+            const int tjr = a.type_s[jslot];
+            const bool jreal = tjr >= 0;
+            const unsigned long long m64 = ((unsigned long long)en.mhi << 32) | en.mlo;
+            const unsigned mb = (unsigned)(m64 >> (jb * M)) & FULL;
+            unsigned act = FULL;
+            if (en.shift == 13) {
+                const int t = jslot - ci * M;
+                act = t >= M ? FULL : (t <= 0 ? 0u : (1u << t) - 1u);
+            }
+            unsigned use = act & mb;   // real, non-excluded pairs of the half list ...
+            float r2[M];
+#pragma unroll
+            for (int k = 0; k < M; ++k) {
+                const float dx = xt[k] + sv.x - pjt.x, dy = yt[k] + sv.y - pjt.y, dz = zt[k] + sv.z - pjt.z;
+                r2[k] = dx * dx + dy * dy + dz * dz;
+                use &= ~((r2[k] < a.rc2 ? 0u : 1u) << k);   // ... now within the cut-off
+            }
+            if (__ballot(valid && use) == 0ull) continue;   // none in the pass: no thresholds needed
             // cluster-pair threshold from the sort-time geometry
             const float4 jl = a.bbj_lo[en.cj], jh = a.bbj_hi[en.cj];
             const float d2bb = sq3(axis_gap(jl.x, jh.x, ilo.x + sv.x, ihi.x + sv.x),
@@ -110,26 +128,15 @@ __global__ __launch_bounds__(64 * kRecountWaves) void k_recount(RecountArgs a) {
             int kb = (int)floorf((tau - a.rc) / a.db);
             if (!valid || kb < 0) continue;   // listed even without a buffer: never missed
             if (kb >= a.nbins) kb = a.nbins - 1;
-            const unsigned long long m64 = ((unsigned long long)en.mhi << 32) | en.mlo;
-            const unsigned mb = (unsigned)(m64 >> (jb * M)) & FULL;
-            unsigned act = FULL;
-            if (en.shift == 13) {
-                const int t = jslot - ci * M;
-                act = t >= M ? FULL : (t <= 0 ? 0u : (1u << t) - 1u);
-            }
-            const unsigned use = act & mb;   // real, non-excluded pairs of the half list
-            const int tj = min(max(a.type_s[jslot], 0), a.nt - 1);
+            const int tj = min(max(tjr, 0), a.nt - 1);
             float acc = 0.0f;
 #pragma unroll
             for (int k = 0; k < M; ++k) {
                 if (!((use >> k) & 1u)) continue;
-                const float dx = xt[k] + sv.x - pjt.x, dy = yt[k] + sv.y - pjt.y, dz = zt[k] + sv.z - pjt.z;
-                const float r2 = dx * dx + dy * dy + dz * dz;
-                if (!(r2 < a.rc2)) continue;
-                const float rinv = __builtin_amdgcn_rsqf(r2);
+                const float rinv = __builtin_amdgcn_rsqf(r2[k]);
                 const float rinv2 = rinv * rinv;
-                const float u = r2 * rinv * a.beta;
-                const float ex = __builtin_amdgcn_exp2f(a.c_exp * r2);
+                const float u = r2[k] * rinv * a.beta;
+                const float ex = __builtin_amdgcn_exp2f(a.c_exp * r2[k]);
                 const float P = fmaf(fmaf(fmaf(MXN_EWALD_P3, u, MXN_EWALD_P2), u, MXN_EWALD_P1), u, MXN_EWALD_P0);
                 const float Q = fmaf(fmaf(fmaf(fmaf(MXN_EWALD_Q4, u, MXN_EWALD_Q3), u, MXN_EWALD_Q2), u, MXN_EWALD_Q1), u,
                                      1.0f);
@@ -150,11 +157,6 @@ __global__ __launch_bounds__(64 * kRecountWaves) void k_recount(RecountArgs a) {
         if (h[t] != 0.0) unsafeAtomicAdd(a.hist + t, h[t]);
 }
 
-__global__ void k_zero_d(double *p, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.0;
-}
-
 }  // namespace
 
 namespace mxn {
@@ -163,11 +165,9 @@ namespace mxn {
 int launch_recount(nb_ctx *ctx, const nb_grid *g, const nb_list *l, const float *xyzq_t, const nb_params *p, float c_bb,
                    float db, int nbins, double *hist) {
     hipStream_t st = ctx->stream;
-    k_zero_d<<<(nbins + 255) / 256, 256, 0, st>>>(hist, nbins);
-    int rc = launch_gather(ctx, g, xyzq_t, p->ntypes);
+    int rc = launch_gather(ctx, g, xyzq_t, p->ntypes, hist, nbins);   // which also clears the histogram
     if (rc) return rc;
     RecountArgs a{};
-    a.perm = (const int *)g->perm.p;
     a.type_s = (const int *)g->type_s.p;
     a.xs = (const float4 *)g->xs.p;
     a.xs_now = (const float4 *)g->xs_now.p;
