@@ -516,9 +516,9 @@ __device__ inline void force_item(const ForceArgs &a, const SysView &v, const fl
             add_i(p0, fx[0], fy[0], fz[0]);
             add_i(p1, fx[1], fy[1], fz[1]);
         }
-    } else if constexpr (M == 8 && LM) {
-        // transposed sums (octet o stores i-particle o) in the single-system kernel; the batched kernel keeps
-        // eight wavefront sums (the transposed form takes it to 75 registers and measured 2 % slower there)
+    } else if constexpr (M == 8) {
+        // transposed sums, octet o stores i-particle o: 18 instructions a component where eight wavefront sums
+        // take 48.  In the batched kernel, 64 replicas of 3 k with energies: 409 -> 394 us (8x4), 441 -> 419 us (8x8)
         const float fx = wave_sum8_t(fix, lane), fy = wave_sum8_t(fiy, lane), fz = wave_sum8_t(fiz, lane);
         if ((lane & 7) == 0) mxn::st(v.fi + (long)item * M + (lane >> 3), make_float4(fx, fy, fz, 0.0f));
     } else {
