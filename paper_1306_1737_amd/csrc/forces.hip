@@ -209,6 +209,23 @@ __device__ inline EwPoly ew_poly(const ForceArgs &a) {
     return {a.ep[0], a.ep[1], in_vreg(a.ep[2]), a.ep[3], a.eq[1], a.eq[2], in_vreg(a.eq[3]), a.eq[4]};
 }
 
+// What an excluded pair (bit clear) drops or reads instead, for a pair's bit as a condition (the super-cluster kernel
+// has it as a lane mask) or as a word of copies of it, -1 or 0, which the direct kernels take straight from the mask
+// byte: with the word each pair spends four VALU instructions on it (bit-field extract, add, and, insert) instead of five
+// and no compare: 64 replicas of 3 k 388 -> 381 us a launch, 96 k with the virial 114.7 -> 112.2 us.  (A whole block
+// of zero rows, so that one 24-bit multiply-add forms the row's offset, takes one instruction less and is slower:
+// 402 and 114.8 us.)
+__device__ inline float kept(bool bit, float x) { return bit ? x : 0.0f; }
+__device__ inline float kept(int bits, float x) { return __int_as_float(bits & __float_as_int(x)); }
+__device__ inline int lj_row(bool bit, int off) { return bit ? off : 0; }
+__device__ inline int lj_row(int bits, int off) { return bits & off; }
+__device__ inline float erfc_part(bool bit) { return bit ? 0.0f : -1.0f; }
+__device__ inline float erfc_part(int bits) {   // (the compiler turns the same expression back into the compare)
+    float x;
+    asm("v_bfi_b32 %0, %1, 0, -1.0" : "=v"(x) : "v"(bits));
+    return x;
+}
+
 // Force factor F/r of one pair within the cut-off, and its energy terms
 // added to el (12 x Lennard-Jones) and ec (Coulomb).  Coulomb variants
 // (ELEC): 0 Ewald with erfc from a rational approximation; 1 reaction field,
@@ -221,9 +238,9 @@ __device__ inline EwPoly ew_poly(const ForceArgs &a) {
 // LJ row).  ljoff: byte offset of the type pair's row of the LDS table.  Both terms are
 // gathered as F/r = (qq T + B / r^6) / r^2 with T = r F_Coulomb / qq (1/r
 // for plain Coulomb) and B = 12 C12 / r^6 - 6 C6; 12 V_LJ = (B - 6 C6) / r^6.
-template <bool ENER, int ELEC>
+template <bool ENER, int ELEC, class BIT>
 __device__ inline float pair_term(const ForceArgs &a, const EwPoly &ew, const float4 *ljt, const float2 *tab, float r2,
-                                  float qq, bool bit, int ljoff, float &el, float &ec) {
+                                  float qq, BIT bit, int ljoff, float &el, float &ec) {
     const float rinv = __builtin_amdgcn_rsqf(r2);
     const float rinv2 = rinv * rinv;
     float T, vc;
@@ -234,11 +251,11 @@ __device__ inline float pair_term(const ForceArgs &a, const EwPoly &ew, const fl
         const float P = fmaf(fmaf(fmaf(ew.p3, r, ew.p2), r, ew.p1), r, ew.p0);
         const float Q = fmaf(fmaf(fmaf(fmaf(ew.q4, r, ew.q3), r, ew.q2), r, ew.q1), r, 1.0f);
         // erfc for an interacting pair, erfc - 1 = -erf(beta r) for an excluded one
-        const float em = fmaf(ex * P, __builtin_amdgcn_rcpf(Q), bit ? 0.0f : -1.0f);
+        const float em = fmaf(ex * P, __builtin_amdgcn_rcpf(Q), erfc_part(bit));
         vc = em * rinv;
         T = fmaf(a.c2bpi, ex, vc);
     } else if (ELEC == 1) {
-        const float einv = bit ? rinv : 0.0f;
+        const float einv = kept(bit, rinv);
         vc = einv + fmaf(a.krf, r2, -a.crf);
         T = fmaf(-a.k2rf, r2, einv);
     } else {
@@ -246,11 +263,11 @@ __device__ inline float pair_term(const ForceArgs &a, const EwPoly &ew, const fl
         const int i0 = (int)t;
         const float eps = t - (float)i0;
         const float2 g0 = tab[i0], g1 = tab[i0 + 1];
-        const float einv = bit ? rinv : 0.0f;
+        const float einv = kept(bit, rinv);
         vc = einv - fmaf(eps, g1.y - g0.y, g0.y);
         T = fmaf(-fmaf(eps, g1.x - g0.x, g0.x), r2, einv);
     }
-    const float4 lj = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(ljt) + (bit ? ljoff : 0));
+    const float4 lj = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(ljt) + lj_row(bit, ljoff));
     const float rinv6 = rinv2 * rinv2 * rinv2;
     const float B = fmaf(lj.y, rinv6, -lj.x);
     const float fsc = rinv2 * fmaf(qq, T, B * rinv6);
@@ -267,12 +284,12 @@ __device__ inline float pair_term(const ForceArgs &a, const EwPoly &ew, const fl
 // pair, else M).  With LM (the single-system kernel) which lanes take part is
 // decided in scalar registers, without branches: live (the lanes with lv),
 // cleared for a dummy i-particle, and the compare k < tri straight into a
-// lane mask; the exclusion bits become a lane mask the same way, read with
-// inverse_ballot.  Without LM (the batched kernel) the tests are per-lane
+// lane mask.  Without LM (the batched kernel) the tests are per-lane
 // bit tests of an activity mask; each form measured faster in its kernel
 // (single 96k box 95.5 against 100.9 us, batch of 256 replicas 3.57 against
 // 3.75 ms).  Measured slower and not used: a copy of the pass without
-// exclusion handling for passes that have none; a branch-free body whose
+// exclusion handling for passes that have none (the two copies' sums take 20
+// more registers, 5 wavefronts a SIMD instead of 7: 82.9 -> 91.2 us); a branch-free body whose
 // eight i-particle chains the compiler can interleave (132 registers).
 template <int M, bool ENER, int ELEC, bool LM>
 __device__ inline void pair_pass(const ForceArgs &a, const EwPoly &ew, const float4 *ljt, const float2 *tab, const float (&xi)[M],
@@ -287,16 +304,14 @@ __device__ inline void pair_pass(const ForceArgs &a, const EwPoly &ew, const flo
     for (int k = 0; k < M; ++k) {
         const float dx = xi[k] - xj, dy = yi[k] - yj, dz = zi[k] - zj;
         const float r2 = dx * dx + dy * dy + dz * dz;
-        bool in, bit;
+        bool in;
+        const int bit = (int)(mb << (31 - k)) >> 31;
         if (LM) {
             const unsigned long long am =
                 (((ireal >> k) & 1u) ? live : 0ull) & __builtin_amdgcn_ballot_w64(k < tri);
-            const unsigned long long bm = __builtin_amdgcn_ballot_w64((mb >> k) & 1u);
             in = (r2 < a.rc2) & __builtin_amdgcn_inverse_ballot_w64(am);
-            bit = __builtin_amdgcn_inverse_ballot_w64(bm);
         } else {
             in = r2 < rc2l && ((act >> k) & 1u);
-            bit = (mb >> k) & 1u;
         }
         if (in) {
             const float fsc = pair_term<ENER, ELEC>(a, ew, ljt, tab, r2, qi[k] * qj, bit, ti[k] + tj, el, ec);
