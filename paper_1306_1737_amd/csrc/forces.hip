@@ -281,13 +281,11 @@ __device__ inline float pair_term(const ForceArgs &a, const EwPoly &ew, const fl
 // One pass of the direct kernel's inner loop: this lane's j-particle against
 // the M i-particles.  lv: this lane holds a real j-particle of a valid entry;
 // tri: i-slots below it take part (slot(i) < slot(j) for the self cluster
-// pair, else M).  With LM (the single-system kernel) which lanes take part is
-// decided in scalar registers, without branches: live (the lanes with lv),
-// cleared for a dummy i-particle, and the compare k < tri straight into a
-// lane mask.  Without LM (the batched kernel) the tests are per-lane
-// bit tests of an activity mask; each form measured faster in its kernel
-// (single 96k box 95.5 against 100.9 us, batch of 256 replicas 3.57 against
-// 3.75 ms).  Measured slower and not used: a copy of the pass without
+// pair, else M).  Which lanes take part is decided with LM in scalar registers,
+// without branches: live (the lanes with lv), cleared for a dummy i-particle,
+// and the compare k < tri straight into a lane mask; without LM by per-lane bit
+// tests of an activity mask.  Each caller takes the form that measured faster
+// in its kernel (force_item's LM).  Measured slower and not used: a copy of the pass without
 // exclusion handling for passes that have none (the two copies' sums take 20
 // more registers, 5 wavefronts a SIMD instead of 7: 82.9 -> 91.2 us); a branch-free body whose
 // eight i-particle chains the compiler can interleave (132 registers).
@@ -436,7 +434,7 @@ __device__ inline double item_sum8_t(const double (&v)[9], int lane) {
 // gfx950: it costs registers and occupancy for no gain.)
 // OWN (small systems): particles are read through the permutation and moved to
 // their image here, with the gather's own operations, instead of from xs_now.
-template <int M, int N, bool ENER, bool VIR, bool ACC64, int ELEC, bool LM = true, bool OWN = false>
+template <int M, int N, bool ENER, bool VIR, bool ACC64, int ELEC, bool LM, bool OWN = false>
 __device__ inline void force_item(const ForceArgs &a, const SysView &v, const float4 *ljt, const float2 *tab,
                                   const float4 *svec, int item, int lane) {
     using acc_t = typename std::conditional<ACC64, double, float>::type;
@@ -589,7 +587,11 @@ __global__ __launch_bounds__(256) void k_forces(ForceArgs a) {
     const long item = xcd_item(total, 4, threadIdx.x >> 6);
     if (item < 0) return;
     const SysView v = make_view(a.xs_now, a.type_s, a.fj, a.fi, a.jpos, a.items, a.entries, a.partials, a.pstride, 0);
-    force_item<M, N, ENER, VIR, ACC64, ELEC, true, OWN>(a, v, ljt, tab, svec, (int)item, lane);
+    // lane masks, us with them / with bit tests a launch: Ewald with energies, 96 k 91.6 / 94.2 (8x8), 86.5 / 92.8
+    // (8x4), 111.9 / 115.7 (4x8), 12 k 18.3 / 19.0 (8x4).  Bit tests: reaction field, 96 k 8x8 63.8 / 60.0, 24 k
+    // 27.0 / 26.7; a small system's forces alone, 12 k 19.2 / 18.8 (8x8)
+    constexpr bool LM = ELEC != 1 && (ENER || !OWN);
+    force_item<M, N, ENER, VIR, ACC64, ELEC, LM, OWN>(a, v, ljt, tab, svec, (int)item, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -1259,6 +1261,7 @@ __device__ inline void batch_item(const ForceArgs &a, const BatchArgs &b, const 
     const RepDesc &d = b.rep[r];
     const SysView v =
         make_view(d.xs_now, d.type_s, d.fj, d.fi, d.jpos, d.items, d.entries, b.partials, b.pstride, d.pbase);
+    // bit tests: 64 replicas of 3 k 381 us a launch (5240 a pass of ten), with lane masks 5465 a pass
     force_item<M, N, ENER, VIR, true, ELEC, false>(a, v, ljt, tab, d.shiftvec, (int)(idx - b.item_off[r]), lane);
 }
 
