@@ -176,10 +176,11 @@ __global__ __launch_bounds__(256) void k_mlp_step(MlpArgs a) {
 
 // Sum of the workgroups' gradient rows (64 parameters per workgroup; each of its wavefronts adds every
 // fourth row, the four sums are added in order), then Adam or the gradient output; the loss is value NPARAM.
+// Summed in FP64, which costs no time here (the launch waits for the rows' loads) and rounds each value once.
 __global__ __launch_bounds__(256) void k_mlp_finish(MlpArgs a, int nparts) {
-    __shared__ float red[4][64];
+    __shared__ double red[4][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, i = blockIdx.x * 64 + lane;
-    float s = 0.0f;
+    double s = 0.0;
     if (i <= NPARAM) {
 #pragma unroll 8
         for (int k = w; k < nparts; k += 4) s += a.parts[(size_t)k * kMlpRow + i];
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(256) void k_mlp_finish(MlpArgs a, int nparts) {
     red[w][lane] = s;
     __syncthreads();
     if (w > 0 || i > NPARAM) return;
-    const float g = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+    const float g = (float)(((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane]);
     if (i == NPARAM) {
         if (a.loss) *a.loss = g / (float)a.batch;
     } else if (a.grad_out) {
