@@ -65,12 +65,27 @@ void release(DevBuf &b) {
     b.mem.reset();
 }
 
+// ensure() for memory that the caller can do without: a refusal leaves no trace of itself, neither HIP's last error,
+// which the launches that follow would report as theirs, nor the library's.
+static bool try_ensure(const nb_ctx *c, DevBuf &b, size_t bytes) {
+    if (bytes <= b.bytes && b.p) return true;
+    const std::string last = g_last_error;
+    if (ensure(c, b, bytes) == NB_OK) return true;
+    (void)hipGetLastError();
+    g_last_error = last;
+    return false;
+}
+
 void *StreamScratch::get(const nb_ctx *c, size_t bytes) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return nullptr;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (cap != hipStreamCaptureStatusNone) return nullptr;
     for (Entry &e : entry) {
         if (e.buf.p && e.stream != c->stream) continue;
-        if (ensure(c, e.buf, bytes) != NB_OK) return nullptr;
+        if (!try_ensure(c, e.buf, bytes)) return nullptr;
         e.stream = c->stream;
         return e.buf.p;
     }
