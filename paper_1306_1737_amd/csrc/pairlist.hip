@@ -1140,7 +1140,8 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
         const long size = mx + mx / 4 + 8;
         if (size * nregions > (1L << 31) - 1) return fail(NB_ERR_OOM, "nb_pairlist_build: list larger than 2^31 entries");
         const long ce = size * nregions;
-        if (ce > l->cap_entries) {
+        const bool grows = ce > l->cap_entries;
+        if (grows) {
             int rc = ensure(l->ctx, l->entries, (size_t)ce * sizeof(nb_jentry));
             if (rc) return rc;
             l->cap_entries = ce;
@@ -1149,16 +1150,19 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
         // GPU is not filled, and a shorter chain per wavefront ends sooner.  One pass against four: 900 atoms 8x8
         // 12.1 against 15.8 us a call, 3000 (4x4) 20.1 against 21.6; 12 000 (8x4) two passes as four, one 6 %
         // slower (15 k items); 24 000 and more four.  (The capacity bound keeps lists of very uneven regions, and
-        // so the scratch nb_forces_noalloc needs for them, as they were.)
+        // so the scratch nb_forces_noalloc needs for them, as they were.)  A list whose entries fit the storage it
+        // has keeps that storage, which captured force calls read: shorter items only where they fit it too.
         const int full = item_entries(g->nn);
+        const auto items_cap = [&](int per) { return ce / per + nregions + 256; };   // count/per + 1 for each region
         l->per_item = full;
         l->est_items = ctx->h_pinned[1];
         for (int k = 2; k > 0 && !l->batched && l->per_item == full; --k)
-            if (ctx->h_pinned[3 + k] <= kSmallItems && ce / (full >> k) + nregions <= 8 * kSmallItems) {
+            if (ctx->h_pinned[3 + k] <= kSmallItems && ce / (full >> k) + nregions <= 8 * kSmallItems &&
+                (grows || items_cap(full >> k) <= l->cap_items)) {
                 l->per_item = full >> k;
                 l->est_items = ctx->h_pinned[3 + k];
             }
-        const long cit = ce / l->per_item + nregions + 256;   // each region: at most count/per-item + 1 items
+        const long cit = items_cap(l->per_item);
         if (cit > l->cap_items) {
             int rc = ensure(l->ctx, l->items, (size_t)cit * sizeof(int4));
             if (rc) return rc;
