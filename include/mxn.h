@@ -209,8 +209,8 @@ enum {
  *   list      in/out: NULL creates, otherwise reused
  * Storage: each (i-cluster, search part) owns an equal region of the entry
  * array.  A synchronous build (no NB_LIST_ASYNC; also the first build of a
- * handle and any build after the grid's capacity changed) counts the
- * entries, sizes every region to the largest count plus a quarter plus 8
+ * handle and any build after the grid's capacity or cluster shape changed)
+ * counts the entries, sizes every region to the largest count plus a quarter plus 8
  * (synchronising once), then fills the regions.  An asynchronous build
  * searches once and fills the regions, with no host synchronisation (it can
  * be captured in a graph); a region that would overflow, or more entries

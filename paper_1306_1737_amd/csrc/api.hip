@@ -938,7 +938,7 @@ int nb_batch_bind_topology(nb_batch *b, const int *const *type, const int *const
     int rc = NB_OK;
     for (int r = 0; r < b->n_rep && rc == NB_OK; ++r) {
         nb_list *l = b->lists[r];
-        if (l->resv_parts != 1 || l->resv_nci != b->grids[r]->slots_cap / b->grids[r]->m)
+        if (l->resv_parts != 1 || !reserved_for(l, b->grids[r]))
             rc = launch_pairlist(l, excl_off[r], excl_idx[r], true, false);
     }
     c->search_parts = saved;
@@ -961,7 +961,7 @@ static int rebuild_refresh(nb_batch *b) {
         nb_grid *g = b->grids[r];
         nb_list *l = b->lists[r];
         if (!grid_batchable(g)) return fail(NB_ERR_UNSUPPORTED, "nb_batch_rebuild: a replica's grid has too many columns");
-        if (l->resv_parts == 0 || l->resv_nci != g->slots_cap / g->m || l->grid != g)
+        if (!reserved_for(l, g) || l->grid != g)
             return fail(NB_ERR_STATE, "nb_batch_rebuild: every replica's list needs a synchronous build on its grid");
         fill_grid_job(gj.data() + gs * r, g, b->xyzq[r], b->type[r]);
         fill_list_job(lj.data() + ls * r, l, b->excl_off[r], b->excl_idx[r]);

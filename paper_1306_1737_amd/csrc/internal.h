@@ -171,6 +171,7 @@ struct nb_list {
     mxn::DevBuf fj, fi;
     int resv_parts = 0;        // search parts of the reserved layout (0: none yet)
     int resv_nci = 0;          // i-cluster capacity of the reserved layout
+    int resv_m = 0, resv_nn = 0;   // its cluster shape
     long resv_size = 0;        // entries per region of the reserved layout
     int per_item = 0;          // entries per work item of the reserved layout
     bool batched = false;      // bound to a batch, which fills the GPU with full items
@@ -258,6 +259,11 @@ void fill_rep_desc(void *out, const nb_grid *g, const nb_list *l, const float *x
 int launch_mlp_step(nb_ctx *ctx, nb_mlp *mlp, const float *X, const float *y, int batch, float lr, float *loss,
                     float *grad_out);
 int launch_mlp_infer(nb_ctx *ctx, const nb_mlp *mlp, const float *X, int batch, float *y);
+
+// The list's regions, counters and rows were sized for grids of this capacity and cluster shape.
+inline bool reserved_for(const nb_list *l, const nb_grid *g) {
+    return l->resv_parts > 0 && l->resv_nci == g->slots_cap / g->m && l->resv_m == g->m && l->resv_nn == g->nn;
+}
 
 // kernel launchers (grid.hip, pairlist.hip, forces.hip)
 int launch_grid_sort(nb_grid *g, const float *xyzq, const int *type);

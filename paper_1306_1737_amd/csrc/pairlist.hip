@@ -1107,11 +1107,11 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
     const int nci_cap = g->slots_cap / g->m;
     SearchArgs a = make_search(l, excl_off, excl_idx);
     // A synchronous build (also the first, and any after the grid's capacity
-    // changed) counts the entries and gives every (i-cluster, part) region the
+    // or cluster shape changed) counts the entries and gives every (i-cluster, part) region the
     // largest count plus a quarter plus 8 (uniform, because a re-sort re-forms
     // the clusters, so a region's next occupant may have any count); later
     // builds search once and fill the regions.
-    const bool reserve = sync || l->resv_parts == 0 || l->resv_nci != nci_cap;
+    const bool reserve = sync || !reserved_for(l, g);
     int parts = l->resv_parts;
     if (reserve) {
         // parts per i-cluster: the largest power of two up to 8 that keeps about 6000
@@ -1180,6 +1180,7 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
         // latches NB_ERR_OVERFLOW like an outgrown region
         const long ent = ctx->h_pinned[2];
         const long rows = std::min(l->cap_entries, ent + ent / 4 + 1024);
+        if (l->resv_nn != g->nn) l->cap_rows = 0;   // rows of another width
         if (rows > l->cap_rows) {
             rc = rc ? rc : ensure(l->ctx, l->fj, (size_t)rows * g->nn * 12);
             if (rc == NB_OK) l->cap_rows = rows;
@@ -1190,6 +1191,8 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
                                                           (int *)l->jcount.p, (int *)l->totals.p);
         l->resv_parts = parts;
         l->resv_nci = nci_cap;
+        l->resv_m = g->m;
+        l->resv_nn = g->nn;
         l->last_entries = ce;
         l->resv_size = size;
     }
@@ -1330,7 +1333,7 @@ int launch_prune(nb_list *in, const nb_list *outer, float r) {
     // the outer list's layout, with buffers of its capacity; new counters start cleared
     const long njc = g->slots_cap / g->nn;
     const size_t nreg = (size_t)outer->resv_nci * kMaxSearchParts + 1;
-    void *old_jc = in->jcount.p, *old_tot = in->totals.p;
+    const size_t old_jc = in->jcount.bytes, old_tot = in->totals.bytes;   // larger: new memory, wherever it lies
     int rc = ensure(in->ctx, in->part_count, nreg * 4);
     rc = rc ? rc : ensure(in->ctx, in->part_start, nreg * 4);
     rc = rc ? rc : ensure(in->ctx, in->part_istart, nreg * 4);
@@ -1345,9 +1348,9 @@ int launch_prune(nb_list *in, const nb_list *outer, float r) {
     rc = rc ? rc : ensure(in->ctx, in->fj, (size_t)outer->cap_rows * g->nn * 12);
     rc = rc ? rc : ensure(in->ctx, in->fi, (size_t)outer->cap_items * g->m * 16);
     if (rc) return rc;
-    if (in->jcount.p != old_jc || in->resv_nci != outer->resv_nci)
+    if (in->jcount.bytes != old_jc || in->resv_nci != outer->resv_nci)
         MXN_HIP(hipMemsetAsync(in->jcount.p, 0, (size_t)nsc * 4, st));
-    if (in->totals.p != old_tot) MXN_HIP(hipMemsetAsync(in->totals.p, 0, 32, st));
+    if (in->totals.bytes != old_tot) MXN_HIP(hipMemsetAsync(in->totals.p, 0, 32, st));
     in->grid = g;
     in->grid_generation = outer->grid_generation;
     in->rlist = r;
@@ -1356,6 +1359,8 @@ int launch_prune(nb_list *in, const nb_list *outer, float r) {
     in->cap_items = outer->cap_items;
     in->resv_parts = outer->resv_parts;
     in->resv_nci = outer->resv_nci;
+    in->resv_m = outer->resv_m;
+    in->resv_nn = outer->resv_nn;
     in->last_entries = outer->last_entries;
     in->per_item = outer->per_item;
     in->est_items = outer->est_items;
