@@ -734,6 +734,8 @@ static int batch_refresh(nb_batch *b, const float *const *xyzq_now, float *const
         caps[r] = l->cap_items + 4;
         if (l->grid_generation != b->grids[r]->generation)
             return fail(NB_ERR_STATE, "nb_batch: a replica's list was built before its grid's last sort");
+        if (b->grids[r]->m != b->m || b->grids[r]->nn != b->nn)
+            return fail(NB_ERR_STATE, "nb_batch: a replica's grid was sorted in another cluster shape: create the batch again");
     }
     std::vector<char> host(ds * b->n_rep);
     std::vector<long> so(b->n_rep + 1), ao(b->n_rep + 1);
@@ -960,6 +962,8 @@ static int rebuild_refresh(nb_batch *b) {
     for (int r = 0; r < n; ++r) {
         nb_grid *g = b->grids[r];
         nb_list *l = b->lists[r];
+        if (g->m != b->m || g->nn != b->nn)
+            return fail(NB_ERR_STATE, "nb_batch_rebuild: a replica's grid was sorted in another cluster shape");
         if (!grid_batchable(g)) return fail(NB_ERR_UNSUPPORTED, "nb_batch_rebuild: a replica's grid has too many columns");
         if (!reserved_for(l, g) || l->grid != g)
             return fail(NB_ERR_STATE, "nb_batch_rebuild: every replica's list needs a synchronous build on its grid");

@@ -45,3 +45,42 @@ def test_rebuilt_in_another_shape(first, then, asynchronous):
         if inner is not None:
             mxn.nb_list_free(inner)
         s.close()
+
+
+def test_batch_refuses_another_shape():
+    """Every call that would run the batch's kernels, before and after a capture."""
+    import torch
+    import paper_1306_1737_amd as mxn
+    box = synth.water_box(400, synth.box_edge_for(400), seed=4)
+    s = GpuSystem(box, (8, 8), RL)
+    try:
+        f = torch.zeros((box.n, 3), dtype=torch.float32, device=s.dev)
+        p = mxn.make_params(RC, BETA, F, s.lj)
+        b = mxn.nb_batch_create(s.ctx, [s.grid], [s.lst], [s.xyzq], [f])
+        mxn.nb_batch_bind_topology(b, [s.type], [s.eo], [s.ei])
+        mxn.nb_batch_capture_cycle(s.ctx, b, 1, p, 0)
+        mxn.nb_batch_replay(s.ctx, b)
+        mxn.nb_sync(s.ctx)
+        first = f.clone()
+        mxn.nb_grid_sort(s.ctx, box.box, s.xyzq, s.type, (8, 4), s.grid)
+        mxn.nb_pairlist_build(s.ctx, s.grid, RL, -1.0, s.eo, s.ei, 0, s.lst)
+        for call in (lambda: mxn.nb_batch_forces(s.ctx, b, p, 0), lambda: mxn.nb_batch_rebuild(s.ctx, b),
+                     lambda: mxn.nb_batch_replay(s.ctx, b), lambda: mxn.nb_batch_capture(s.ctx, b, p, 0),
+                     lambda: mxn.nb_batch_capture_cycle(s.ctx, b, 1, p, 0)):
+            with pytest.raises(mxn.NbError) as e:
+                call()
+            assert e.value.status == mxn.NB_ERR_STATE
+        mxn.nb_sync(s.ctx)
+        assert (f == first).all()
+        mxn.nb_grid_sort(s.ctx, box.box, s.xyzq, s.type, (8, 8), s.grid)   # back in its shape it runs again
+        mxn.nb_pairlist_build(s.ctx, s.grid, RL, -1.0, s.eo, s.ei, 0, s.lst)
+        mxn.nb_batch_forces(s.ctx, b, p, 0)
+        mxn.nb_sync(s.ctx)
+        fr, _, _ = oracle.forces(box.xyz, box.q, box.type, box.box, box.excl_off, box.excl_idx, synth.lj_table_spce(), RC,
+                                 BETA, F)
+        for g in (f, first):
+            g = g.cpu().numpy().astype(np.float64)
+            assert rel_rms(g, fr) <= 1e-5 and max_atom_err(g, fr) <= 1e-4
+        mxn.nb_batch_free(b)
+    finally:
+        s.close()
