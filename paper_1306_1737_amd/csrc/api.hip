@@ -77,6 +77,7 @@ static bool try_ensure(const nb_ctx *c, DevBuf &b, size_t bytes) {
 }
 
 void *StreamScratch::get(const nb_ctx *c, size_t bytes) {
+    if (c->stream == hipStreamPerThread) return nullptr;   // one handle for a stream of every thread
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
         (void)hipGetLastError();

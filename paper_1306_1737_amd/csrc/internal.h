@@ -66,7 +66,8 @@ void release(DevBuf &b);
 // memory, and a call holds mu over its launches, so those of two threads do
 // not interleave.  get() gives null, and the caller takes its one-launch form,
 // while the context's stream is being captured (replays could overlap other
-// calls), for a fifth stream, and without memory.
+// calls), for a fifth stream, for the per-thread default stream (whose one
+// handle names a stream of every thread) and without memory.
 struct StreamScratch {
     struct Entry {
         hipStream_t stream = nullptr;
