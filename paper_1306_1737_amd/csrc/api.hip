@@ -84,13 +84,21 @@ void *StreamScratch::get(const nb_ctx *c, size_t bytes) {
         return nullptr;
     }
     if (cap != hipStreamCaptureStatusNone) return nullptr;
-    for (Entry &e : entry) {
-        if (e.buf.p && e.stream != c->stream) continue;
-        if (!try_ensure(c, e.buf, bytes)) return nullptr;
-        e.stream = c->stream;
-        return e.buf.p;
+    ++calls;
+    Entry *mine = nullptr;   // this stream's buffer, or a free entry, or the one unused for longest
+    for (Entry &e : entry)
+        if (e.buf.p && e.stream == c->stream) mine = &e;
+    for (Entry &e : entry)
+        if (!mine && !e.buf.p) mine = &e;
+    if (!mine) {
+        mine = std::min_element(entry, std::end(entry), [](const Entry &x, const Entry &y) { return x.used < y.used; });
+        if (calls - mine->used <= kIdle) return nullptr;
+        release(mine->buf);
     }
-    return nullptr;
+    if (!try_ensure(c, mine->buf, bytes)) return nullptr;
+    mine->stream = c->stream;
+    mine->used = calls;
+    return mine->buf.p;
 }
 
 static hipEvent_t take_event(nb_ctx *c) {

@@ -66,14 +66,22 @@ void release(DevBuf &b);
 // memory, and a call holds mu over its launches, so those of two threads do
 // not interleave.  get() gives null, and the caller takes its one-launch form,
 // while the context's stream is being captured (replays could overlap other
-// calls), for a fifth stream, for the per-thread default stream (whose one
-// handle names a stream of every thread) and without memory.
+// calls), for a stream beyond those that have a buffer, for the per-thread
+// default stream (whose one handle names a stream of every thread) and without
+// memory.  A buffer that kIdle calls have gone by without goes to the next
+// stream that wants one: freed (which waits for its work, or leaves that to
+// the stream order of the caller's allocator) and requested anew, so programs
+// that move on to other streams keep the faster form, and few enough calls
+// apart that five streams in turn do not free and request on every call.
 struct StreamScratch {
+    static constexpr long kIdle = 64;
     struct Entry {
         hipStream_t stream = nullptr;
         DevBuf buf;
+        long used = 0;   // the call that last took it
     };
     Entry entry[4];
+    long calls = 0;
     std::mutex mu;
     void *get(const ::nb_ctx *c, size_t bytes);   // mu held
     void clear() {

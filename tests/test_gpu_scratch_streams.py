@@ -1,5 +1,6 @@
-"""The scratch of minibatches spread over workgroups on several streams and threads: each stream has rows of its own, and
-the per-thread default stream, one handle for a stream of every thread, gets none."""
+"""The scratch of minibatches spread over workgroups on several streams and threads: each stream has rows of its own, a
+stream beyond the four that have some takes them over once they lie idle, and the per-thread default stream, one handle
+for a stream of every thread, gets none."""
 import threading
 
 import numpy as np
@@ -43,6 +44,33 @@ def test_five_streams_in_turn():
             _check(gs, ls, ref)
         for gs in g[1:4]:
             assert (gs == g[0]).all()   # the same form, rows added in a fixed order
+    finally:
+        _free(ctx, m)
+
+
+def test_a_new_stream_takes_over_idle_rows():
+    import torch
+    import paper_1306_1737_amd as mxn
+    ctx, m, Xd, yd, _, loss, ref = _grad_setup(256)
+    try:
+        streams = [torch.cuda.Stream() for _ in range(5)]
+        spread, fifth = _grads(2)
+        torch.cuda.synchronize()
+        for s in streams[:4]:
+            mxn.nb_set_stream(ctx, s)
+            mxn.nb_mlp_grad(ctx, m, Xd, yd, spread, loss)
+            mxn.nb_sync(ctx)
+        held = mxn.nb_memory_info(ctx)
+        mxn.nb_set_stream(ctx, streams[4])
+        mxn.nb_mlp_grad(ctx, m, Xd, yd, fifth, loss)
+        mxn.nb_sync(ctx)
+        _check(fifth, loss, ref)
+        assert not (fifth == spread).all()   # one workgroup: another order of the sums
+        for _ in range(80):
+            mxn.nb_mlp_grad(ctx, m, Xd, yd, fifth, loss)
+        mxn.nb_sync(ctx)
+        assert (fifth == spread).all()
+        assert mxn.nb_memory_info(ctx) == held
     finally:
         _free(ctx, m)
 
