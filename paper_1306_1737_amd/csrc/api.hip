@@ -780,6 +780,21 @@ static int batch_refresh(nb_batch *b, const float *const *xyzq_now, float *const
     return NB_OK;
 }
 
+// Work items of full length for the replicas' lists.  A list's build or force calls may still run on another stream
+// that the context had, and the next call on the list may come on yet another: both are waited for.
+static int batch_full_items(nb_batch *b) {
+    bool any = false;
+    for (nb_list *l : b->lists) {
+        l->batched = true;
+        any = any || short_items(l);
+    }
+    if (!any) return NB_OK;
+    MXN_HIP(hipDeviceSynchronize());
+    for (nb_list *l : b->lists) CHECK(launch_full_items(l));
+    MXN_HIP(hipStreamSynchronize(b->ctx->stream));
+    return NB_OK;
+}
+
 int nb_batch_create(nb_ctx *c, int n_rep, nb_grid *const *grids, nb_list *const *lists, const float *const *xyzq_now,
                     float *const *f, nb_batch **out) {
     if (!c || n_rep < 1 || !grids || !lists || !xyzq_now || !f || !out)
@@ -804,12 +819,8 @@ int nb_batch_create(nb_ctx *c, int n_rep, nb_grid *const *grids, nb_list *const 
     int ncu = 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || ncu < 1) ncu = 1;
     b->ncu = ncu;
-    int rc = NB_OK;
-    for (int r = 0; r < n_rep && rc == NB_OK; ++r) {
-        lists[r]->batched = true;
-        rc = launch_full_items(lists[r]);
-    }
-    rc = rc ? rc : batch_refresh(b, xyzq_now, f, true);
+    int rc = batch_refresh(b, xyzq_now, f, true);
+    rc = rc ? rc : batch_full_items(b);
     if (rc != NB_OK) {
         nb_batch_free(b);
         return rc;

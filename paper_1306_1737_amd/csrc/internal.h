@@ -276,7 +276,10 @@ inline bool reserved_for(const nb_list *l, const nb_grid *g) {
 
 // kernel launchers (grid.hip, pairlist.hip, forces.hip)
 int launch_grid_sort(nb_grid *g, const float *xyzq, const int *type);
-// work items of full length for a list built with shorter ones (entries and regions stay as they are)
+// a list built with shorter work items, and full-length ones for it (entries and regions stay as they are)
+inline bool short_items(const nb_list *l) {
+    return l->resv_parts > 0 && l->per_item > 0 && l->per_item < item_entries(l->grid->nn);
+}
 int launch_full_items(nb_list *l);
 int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool sync, bool by_distance);
 // noalloc: the device address of the static scratch (nb_forces_noalloc), or null

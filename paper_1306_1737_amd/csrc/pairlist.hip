@@ -1229,7 +1229,7 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
 }
 
 int launch_full_items(nb_list *l) {
-    if (l->resv_parts == 0 || l->per_item == 0 || l->per_item == item_entries(l->grid->nn)) return NB_OK;
+    if (!short_items(l)) return NB_OK;
     l->per_item = item_entries(l->grid->nn);   // capacities hold: fewer items of the same entries
     const int nregions = l->resv_nci * l->resv_parts;
     k_full_items<<<1, 1024, 0, l->ctx->stream>>>(nregions, l->per_item, (const int *)l->part_count.p,
