@@ -185,6 +185,7 @@ struct nb_list {
     int per_item = 0;          // entries per work item of the reserved layout
     bool batched = false;      // bound to a batch, which fills the GPU with full items
     long est_items = 0;        // work items of the last synchronous build (sizes the force-kernel grid)
+    long full_items = 0;       // the same with items of full length
     long cap_rows = 0;         // j-force rows fj holds: the last synchronous build's entries plus a quarter
     long last_entries = 0;     // host copy after a synchronous build
     long grid_generation = -1;

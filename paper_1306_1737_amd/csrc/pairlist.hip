@@ -1155,7 +1155,7 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
         const int full = item_entries(g->nn);
         const auto items_cap = [&](int per) { return ce / per + nregions + 256; };   // count/per + 1 for each region
         l->per_item = full;
-        l->est_items = ctx->h_pinned[1];
+        l->est_items = l->full_items = ctx->h_pinned[1];
         for (int k = 2; k > 0 && !l->batched && l->per_item == full; --k)
             if (ctx->h_pinned[3 + k] <= kSmallItems && ce / (full >> k) + nregions <= 8 * kSmallItems &&
                 (grows || items_cap(full >> k) <= l->cap_items)) {
@@ -1231,6 +1231,7 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
 int launch_full_items(nb_list *l) {
     if (!short_items(l)) return NB_OK;
     l->per_item = item_entries(l->grid->nn);   // capacities hold: fewer items of the same entries
+    l->est_items = l->full_items;
     const int nregions = l->resv_nci * l->resv_parts;
     k_full_items<<<1, 1024, 0, l->ctx->stream>>>(nregions, l->per_item, (const int *)l->part_count.p,
                                                  (int *)l->part_istart.p, (int *)l->totals.p);
@@ -1364,6 +1365,7 @@ int launch_prune(nb_list *in, const nb_list *outer, float r) {
     in->last_entries = outer->last_entries;
     in->per_item = outer->per_item;
     in->est_items = outer->est_items;
+    in->full_items = outer->full_items;
     in->cap_rows = outer->cap_rows;
     in->resv_size = outer->resv_size;
     in->sci_valid = false;

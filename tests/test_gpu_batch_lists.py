@@ -1,10 +1,11 @@
-"""What a batch does to its replicas' lists: work items of full length, but no kernel on a list that is still being built
-on another stream, and nothing if the batch could not be created."""
+"""What a batch does to its replicas' lists: work items of full length, the estimate that sizes its launches with
+them, no kernel on a list that is still being built on another stream, and nothing if the batch could not be created."""
 import numpy as np
 import pytest
 
 import oracle
 import synth
+from _internals import load
 from _nb import F, GpuSystem, max_atom_err, rel_rms
 
 pytestmark = pytest.mark.gpu
@@ -78,5 +79,21 @@ def test_a_batch_that_is_not_created_changes_no_list():
         assert _items(s) == short
         _build(s)
         assert _items(s) == short
+    finally:
+        s.close()
+
+
+def test_estimate_of_full_items(tmp_path):
+    import paper_1306_1737_amd as mxn
+    internals = load(str(tmp_path))
+    s = _system()
+    try:
+        short = _items(s)
+        assert internals.list_est_items(s.lst) == short
+        b, _ = _batch(s)
+        full = _items(s)
+        assert full < short
+        assert internals.list_est_items(s.lst) == full
+        mxn.nb_batch_free(b)
     finally:
         s.close()
