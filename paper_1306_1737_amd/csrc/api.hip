@@ -784,14 +784,23 @@ static int batch_refresh(nb_batch *b, const float *const *xyzq_now, float *const
 // that the context had, and the next call on the list may come on yet another: both are waited for.
 static int batch_full_items(nb_batch *b) {
     bool any = false;
-    for (nb_list *l : b->lists) {
-        l->batched = true;
-        any = any || short_items(l);
+    for (const nb_list *l : b->lists) any = any || short_items(l);
+    if (any) {
+        MXN_HIP(hipDeviceSynchronize());
+        for (nb_list *l : b->lists) CHECK(launch_full_items(l));
+        MXN_HIP(hipStreamSynchronize(b->ctx->stream));
     }
-    if (!any) return NB_OK;
-    MXN_HIP(hipDeviceSynchronize());
-    for (nb_list *l : b->lists) CHECK(launch_full_items(l));
-    MXN_HIP(hipStreamSynchronize(b->ctx->stream));
+    try {
+        b->alive = std::make_shared<char>();
+        for (nb_list *l : b->lists) {
+            auto &of = l->batches;
+            of.erase(std::remove_if(of.begin(), of.end(), [](const std::weak_ptr<char> &w) { return w.expired(); }),
+                     of.end());
+            of.push_back(b->alive);
+        }
+    } catch (const std::bad_alloc &) {
+        return fail(NB_ERR_OOM, "nb_batch_create: host allocation");
+    }
     return NB_OK;
 }
 

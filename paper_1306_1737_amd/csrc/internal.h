@@ -183,7 +183,7 @@ struct nb_list {
     int resv_m = 0, resv_nn = 0;   // its cluster shape
     long resv_size = 0;        // entries per region of the reserved layout
     int per_item = 0;          // entries per work item of the reserved layout
-    bool batched = false;      // bound to a batch, which fills the GPU with full items
+    std::vector<std::weak_ptr<char>> batches;   // that it is bound to; each fills the GPU with full items
     long est_items = 0;        // work items of the last synchronous build (sizes the force-kernel grid)
     long full_items = 0;       // the same with items of full length
     long cap_rows = 0;         // j-force rows fj holds: the last synchronous build's entries plus a quarter
@@ -199,6 +199,12 @@ struct nb_list {
     mutable int sci_S = 0, sci_per_item = 0;
     mutable bool sci_valid = false;   // built from the list's latest build
     bool sci_volatile = false;        // rebuilt inside a captured graph: the view is rebuilt by every call
+
+    bool batched() const {
+        for (const std::weak_ptr<char> &b : batches)
+            if (!b.expired()) return true;
+        return false;
+    }
 };
 
 struct nb_batch {
@@ -206,6 +212,7 @@ struct nb_batch {
     int n_rep = 0, m = 0, nn = 0, waves = 4, ncu = 1;
     long grid_waves = 0;   // main force-launch wavefronts (0: from the lists' item estimates)
     long total_slots = 0, total_atoms = 0, pstride = 0;
+    std::shared_ptr<char> alive;   // lists bound to the batch hold a weak reference (either may be freed first)
     std::vector<nb_grid *> grids;
     std::vector<nb_list *> lists;
     std::vector<long> generations;

@@ -1156,7 +1156,7 @@ int launch_pairlist(nb_list *l, const int *excl_off, const int *excl_idx, bool s
         const auto items_cap = [&](int per) { return ce / per + nregions + 256; };   // count/per + 1 for each region
         l->per_item = full;
         l->est_items = l->full_items = ctx->h_pinned[1];
-        for (int k = 2; k > 0 && !l->batched && l->per_item == full; --k)
+        for (int k = 2; k > 0 && !l->batched() && l->per_item == full; --k)
             if (ctx->h_pinned[3 + k] <= kSmallItems && ce / (full >> k) + nregions <= 8 * kSmallItems &&
                 (grows || items_cap(full >> k) <= l->cap_items)) {
                 l->per_item = full >> k;

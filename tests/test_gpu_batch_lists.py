@@ -1,5 +1,6 @@
-"""What a batch does to its replicas' lists: work items of full length, the estimate that sizes its launches with
-them, no kernel on a list that is still being built on another stream, and nothing if the batch could not be created."""
+"""What a batch does to its replicas' lists: work items of full length while it is there, the estimate that sizes its
+launches with them, short items again once it is gone, nothing if it could not be created, and no kernel on a list that
+is still being built on another stream."""
 import numpy as np
 import pytest
 
@@ -34,6 +35,62 @@ def _items(s):
     return mxn.nb_list_info(s.lst)[1]
 
 
+def test_estimate_of_full_items(tmp_path):
+    import paper_1306_1737_amd as mxn
+    internals = load(str(tmp_path))
+    s = _system()
+    try:
+        short = _items(s)
+        assert internals.list_est_items(s.lst) == short
+        b, _ = _batch(s)
+        full = _items(s)
+        assert full < short
+        assert internals.list_est_items(s.lst) == full
+        mxn.nb_batch_free(b)
+    finally:
+        s.close()
+
+
+def test_short_items_after_the_batch():
+    import paper_1306_1737_amd as mxn
+    s = _system()
+    try:
+        short = _items(s)
+        b0, _ = _batch(s)
+        b1, _ = _batch(s)
+        full = _items(s)
+        assert full < short
+        mxn.nb_batch_free(b0)
+        _build(s)
+        assert _items(s) == full    # still bound to the other batch
+        mxn.nb_batch_free(b1)
+        _build(s)
+        assert _items(s) == short
+        b2, _ = _batch(s)
+        mxn.nb_list_free(s.lst)     # lists may go before the batch
+        s.lst = mxn.nb_pairlist_build(s.ctx, s.grid, RL, -1.0, s.eo, s.ei)
+        mxn.nb_batch_free(b2)
+        assert _items(s) == short
+    finally:
+        s.close()
+
+
+def test_a_batch_that_is_not_created_changes_no_list():
+    import paper_1306_1737_amd as mxn
+    s = _system()
+    try:
+        short = _items(s)
+        mxn.nb_grid_sort(s.ctx, s.box.box, s.xyzq, s.type, (8, 8), s.grid)   # the list is now older than its grid
+        with pytest.raises(mxn.NbError) as e:
+            _batch(s)
+        assert e.value.status == mxn.NB_ERR_STATE
+        assert _items(s) == short
+        _build(s)
+        assert _items(s) == short
+    finally:
+        s.close()
+
+
 def test_created_while_a_list_is_built_on_another_stream():
     import torch
     import paper_1306_1737_amd as mxn
@@ -63,37 +120,5 @@ def test_created_while_a_list_is_built_on_another_stream():
         np.testing.assert_allclose(e.cpu().numpy()[0], er, rtol=1e-5, atol=1e-5 * np.abs(er).max())
         mxn.nb_batch_free(batch)
         torch.cuda.synchronize()
-    finally:
-        s.close()
-
-
-def test_a_batch_that_is_not_created_changes_no_list():
-    import paper_1306_1737_amd as mxn
-    s = _system()
-    try:
-        short = _items(s)
-        mxn.nb_grid_sort(s.ctx, s.box.box, s.xyzq, s.type, (8, 8), s.grid)   # the list is now older than its grid
-        with pytest.raises(mxn.NbError) as e:
-            _batch(s)
-        assert e.value.status == mxn.NB_ERR_STATE
-        assert _items(s) == short
-        _build(s)
-        assert _items(s) == short
-    finally:
-        s.close()
-
-
-def test_estimate_of_full_items(tmp_path):
-    import paper_1306_1737_amd as mxn
-    internals = load(str(tmp_path))
-    s = _system()
-    try:
-        short = _items(s)
-        assert internals.list_est_items(s.lst) == short
-        b, _ = _batch(s)
-        full = _items(s)
-        assert full < short
-        assert internals.list_est_items(s.lst) == full
-        mxn.nb_batch_free(b)
     finally:
         s.close()
