@@ -299,14 +299,17 @@ int nb_grid_sort(nb_ctx *c, const double box[3], int n, const float *xyzq, const
     g->inv_x = (float)((double)g->nx / box[0]);
     g->inv_y = (float)((double)g->ny / box[1]);
     g->ncol = g->nx * g->ny;
-    // four z bins per column spacing, about four per j-cluster: a window looked up in them holds an eighth of a
-    // cluster more at either end than the exact one
-    g->nz = (int)std::fmin(std::fmax(std::floor(4.0 * box[2] / s), 1.0), 65536.0);
-    g->inv_z = (float)((double)g->nz / box[2]);
     long cap = (long)n + (long)g->ncol * (g->cmax - 1);
     cap = (cap + g->cmax - 1) / g->cmax * g->cmax;
     if (cap > (1L << 30)) return fail(NB_ERR_ARG, "nb_grid_sort: too many particles");
     g->slots_cap = (int)cap;
+    // four z bins per column spacing, about four per j-cluster: a window looked up in them holds an eighth of a
+    // cluster more at either end than the exact one.  In a box thinner than a column the spacing says little of a
+    // column's clusters: no more than four bins for each of those that the columns' capacity gives it, so that the
+    // index stays within the size of the clusters' own storage (and of an int).
+    const long bins = std::max(1L, 4 * (cap / g->nn) / g->ncol);
+    g->nz = (int)std::fmin(std::fmax(std::floor(4.0 * box[2] / s), 1.0), (double)std::min(bins, 65536L));
+    g->inv_z = (float)((double)g->nz / box[2]);
     const size_t nc = (size_t)g->ncol, ns = (size_t)cap, na = (size_t)n;
     int rc = NB_OK;
     rc = rc ? rc : ensure(g->ctx, g->col_count, nc * 4);
