@@ -268,6 +268,15 @@ int nb_grid_sort(nb_ctx *c, const double box[3], int n, const float *xyzq, const
     if (!ok_shape) return fail(NB_ERR_ARG, "nb_grid_sort: supported shapes are 4x4, 4x8, 8x4, 8x8");
     for (int d = 0; d < 3; ++d)
         if (!(box[d] > 0.0) || !std::isfinite(box[d])) return fail(NB_ERR_ARG, "nb_grid_sort: bad box");
+    // column grid: spacing (max(M,N)/rho)^(1/3), rho = n / V; refused before the handle changes
+    const int cmax = std::max(shape.m, shape.n);
+    const double rho = (double)n / (box[0] * box[1] * box[2]);
+    const double s = std::cbrt((double)cmax / rho);
+    const double nx = std::fmax(std::floor(box[0] / s), 1.0), ny = std::fmax(std::floor(box[1] / s), 1.0);
+    if (!(nx * ny <= (double)(1L << 30))) return fail(NB_ERR_ARG, "nb_grid_sort: too many columns");
+    long cap = (long)n + (long)(nx * ny) * (cmax - 1);
+    cap = (cap + cmax - 1) / cmax * cmax;
+    if (cap > (1L << 30)) return fail(NB_ERR_ARG, "nb_grid_sort: too many particles");
     MXN_HIP(hipSetDevice(c->device));
     nb_grid *g = *grid;
     if (g && g->ctx != c) return fail(NB_ERR_STATE, "nb_grid_sort: grid belongs to another context");
@@ -282,26 +291,18 @@ int nb_grid_sort(nb_ctx *c, const double box[3], int n, const float *xyzq, const
     g->m = shape.m;
     g->nn = shape.n;
     g->cmin = shape.m < shape.n ? shape.m : shape.n;
-    g->cmax = shape.m > shape.n ? shape.m : shape.n;
+    g->cmax = cmax;
     for (int d = 0; d < 3; ++d) {
         g->box[d] = box[d];
         g->Lf[d] = (float)box[d];
         g->invL[d] = 1.0 / (double)g->Lf[d];
     }
-    // column grid: spacing (max(M,N)/rho)^(1/3), rho = n / V
-    const double rho = (double)n / (box[0] * box[1] * box[2]);
-    const double s = std::cbrt((double)g->cmax / rho);
     g->spacing = s;
-    g->nx = (int)std::floor(box[0] / s);
-    g->ny = (int)std::floor(box[1] / s);
-    if (g->nx < 1) g->nx = 1;
-    if (g->ny < 1) g->ny = 1;
+    g->nx = (int)nx;
+    g->ny = (int)ny;
     g->inv_x = (float)((double)g->nx / box[0]);
     g->inv_y = (float)((double)g->ny / box[1]);
     g->ncol = g->nx * g->ny;
-    long cap = (long)n + (long)g->ncol * (g->cmax - 1);
-    cap = (cap + g->cmax - 1) / g->cmax * g->cmax;
-    if (cap > (1L << 30)) return fail(NB_ERR_ARG, "nb_grid_sort: too many particles");
     g->slots_cap = (int)cap;
     // four z bins per column spacing, about four per j-cluster: a window looked up in them holds an eighth of a
     // cluster more at either end than the exact one.  In a box thinner than a column the spacing says little of a

@@ -1,5 +1,6 @@
 """Boxes thinner than a grid column, where the columns hold far less than a cluster each: the grid's storage follows the
-particles, not the box's extent along z, and sort and list are the oracle's."""
+particles, not the box's extent along z, and sort and list are the oracle's.  Boxes so flat that the columns outnumber an int are
+refused, and a grid that was refused a sort still serves its list."""
 import numpy as np
 import pytest
 
@@ -36,3 +37,22 @@ def test_storage_and_list(shape, box, n):
     finally:
         mxn.nb_destroy(ctx)
     _check(xyz, box, shape, 9e-5, -1.0, np.zeros(n + 1), np.zeros(1))
+
+
+@pytest.mark.parametrize("box", [(100.0, 100.0, 1e-9), (100.0, 100.0, 1e-12), (100.0, 100.0, 1e-30), (1e-200, 1e-200, 1.0)])
+def test_too_many_columns(box):
+    import paper_1306_1737_amd as mxn
+    import synth
+    from _nb import GpuSystem
+    w = synth.water_box(300, synth.box_edge_for(300), seed=2)
+    s = GpuSystem(w, (8, 8), 0.7)
+    try:
+        first = s.forces(0.65, 4.6, mxn.NB_ENERGY)
+        for grid in (s.grid, None):
+            with pytest.raises(mxn.NbError) as e:
+                mxn.nb_grid_sort(s.ctx, box, s.xyzq, s.type, (8, 4), grid)
+            assert e.value.status == mxn.NB_ERR_ARG
+        for a, b in zip(first, s.forces(0.65, 4.6, mxn.NB_ENERGY)):
+            np.testing.assert_array_equal(a, b)
+    finally:
+        s.close()
