@@ -1169,8 +1169,10 @@ struct RepDesc {
     const int *totals;
     const float4 *shiftvec;
     float Lx, Ly, Lz;
+    int pad;      // tables are compared byte by byte: no padding
     long pbase;   // first partial slot of this replica
 };
+static_assert(sizeof(RepDesc) == 17 * sizeof(void *) + 6 * sizeof(int) + sizeof(long), "RepDesc has padding");
 
 struct BatchArgs {
     const RepDesc *rep;

@@ -163,7 +163,10 @@ struct SortArgs {
     int nz;
     float inv_z;
     float bins_z;                                // z bins of the column sort per length
+    int pad;                                     // job tables are compared byte by byte: no padding
 };
+static_assert(sizeof(SortArgs) == 14 * sizeof(void *) + 2 * sizeof(int) + 5 * sizeof(void *) + 4 * sizeof(int),
+              "SortArgs has padding");
 
 // Bounding box of each cluster of `size` slots among clusters [c0, c1), one thread per cluster
 // (dummies skipped: a cluster of dummies only keeps the empty box, lo = +inf, hi = -inf).  lo.w carries
@@ -437,6 +440,8 @@ struct GridJob {
     int *col_hist, *col_start, *nslots;
     float4 *shiftvec;
 };
+static_assert(sizeof(GridJob) == sizeof(WrapArgs) + sizeof(SortArgs) + 6 * sizeof(int) + 4 * sizeof(void *),
+              "GridJob has padding");
 
 __device__ inline int job_of(const int *off, int n, int b) {
     int lo = 0, hi = n - 1;   // last r with off[r] <= b
@@ -500,7 +505,7 @@ static SortArgs make_sort(const nb_grid *g, const int *type) {
                     (float4 *)g->colbb.p, (int *)g->type_s.p, (int *)g->perm.p, (int *)g->img_s.p,
                     (int *)g->slot_of.p, g->ctx->d_flags, g->m, g->nn, (float4 *)g->bbi_lo.p, (float4 *)g->bbi_hi.p,
                     (float4 *)g->bbj_lo.p, (float4 *)g->bbj_hi.p, (int2 *)g->zfirst.p, g->nz, g->inv_z,
-                    (float)(kSortBins / g->box[2])};
+                    (float)(kSortBins / g->box[2]), 0};
 }
 
 size_t grid_job_size() { return sizeof(GridJob); }

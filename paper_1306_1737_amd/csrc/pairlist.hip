@@ -44,7 +44,7 @@ struct SearchArgsT {
     P<float> keys;          // bounding-box distance^2 of each entry (or null)
     P<int> jcount;          // entries per j-cluster, kRankSets counters jstride apart (fill pass; zero before it)
     P<int> jrank;           // each written entry's rank among its j-cluster's entries of the workgroup's set
-    int nci_cap, parts, jstride;
+    int nci_cap, parts, jstride, pad;    // no padding: job tables are compared byte by byte
 };
 using SearchArgs = SearchArgsT<plain>;
 using SearchArgsG = SearchArgsT<gptr>;
@@ -948,6 +948,10 @@ struct ListJob {
     SearchArgs a;
     FinishArgs f;
 };
+static_assert(sizeof(SearchArgs) == 20 * sizeof(void *) + 16 * sizeof(int) &&
+                  sizeof(FinishArgs) == 11 * sizeof(void *) + 2 * sizeof(long) + 8 * sizeof(int) &&
+                  sizeof(ListJob) == sizeof(SearchArgs) + sizeof(FinishArgs),
+              "a job table has padding");
 
 enum { LS_SEARCH, LS_NSTAGES };   // one workgroup per four regions: the search and the last pass
 
