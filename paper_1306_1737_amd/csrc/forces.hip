@@ -1028,8 +1028,8 @@ __global__ __launch_bounds__(256) void k_fold(ForceArgs a) {
 // interacting pairs within rc, c[2] excluded pairs within rc.  With one
 // wavefront per item the call was bound by the atomics on these three words,
 // 37 ns an item; persistent workgroups add once each (96 000 atoms 8x8 969 ->
-// 150 us a call, 3000 atoms 4x4 with short items 234 -> 63, of which 60 are
-// the call's two synchronisations).
+// 150 us a call, 3000 atoms 4x4 with short items 234 -> 63, where 900 atoms,
+// next to nothing but the call's two synchronisations, take 62).
 constexpr int kStatsGroups = 1024;
 template <int M, int N>
 __global__ __launch_bounds__(256) void k_stats(ForceArgs a, unsigned long long *c) {

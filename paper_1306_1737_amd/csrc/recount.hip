@@ -47,7 +47,10 @@ __device__ inline float axis_gap(float jlo, float jhi, float ilo, float ihi) {
 }
 
 constexpr int kRecountWaves = 8;       // wavefronts per workgroup
-constexpr int kRecountGroups = 768;    // most workgroups: persistent, so that few histograms are flushed
+// Most workgroups: persistent, so that few histograms are flushed, and as many as the GPU holds at once, two to a CU
+// with 8 i-particles (109 registers), three with 4.  The 96 000-atom 8x8 list to 1.4 nm takes 137 us with 512 and 169
+// with 768, whose last third waits for the first two (1.0 nm: 83 and 92); 24 000 atoms 4x8 to 1.4 nm 54 and 46.
+constexpr int recount_groups(int m) { return m == 8 ? 512 : 768; }
 constexpr int kRecountLdsBins = 2048;  // larger histograms are added to in memory
 
 template <int M, int N>
@@ -193,7 +196,7 @@ int launch_recount(nb_ctx *ctx, const nb_grid *g, const nb_list *l, const float 
     a.nbins = nbins;
     a.hist = hist;
     const long need = (std::min(l->cap_items, l->est_items + l->est_items / 4 + 256) + kRecountWaves - 1) / kRecountWaves;
-    const int nb = (int)std::max(1L, std::min(need, (long)kRecountGroups));
+    const int nb = (int)std::max(1L, std::min(need, (long)recount_groups(g->m)));
     const size_t lds = (size_t)p->ntypes * p->ntypes * sizeof(float4) +
                        (nbins <= kRecountLdsBins ? (size_t)nbins * sizeof(double) : 0);
     if (g->m == 4 && g->nn == 4) k_recount<4, 4><<<nb, 64 * kRecountWaves, lds, st>>>(a);
