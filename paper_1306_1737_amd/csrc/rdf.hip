@@ -203,9 +203,13 @@ int launch_rdf(nb_ctx *ctx, const nb_grid *g, const nb_list *l, float r_max, int
     const int nb = (int)std::max(1L, std::min(need, (long)kRdfGroups));
     const size_t lds = rdf_lds_bytes(nbins, nt);
     std::lock_guard<std::mutex> lock(ctx->rdf_parts.mu);
-    // A workgroup's atomics take about 32 ns (1500 counted bins, 46 G atomics/s over the whole chip, wherever they
-    // go), the summing launch about 5 us.
-    if (nb > 128) a.parts = (unsigned *)ctx->rdf_parts.get(ctx, (size_t)nt * nt * nbins * kRdfGroups * sizeof(unsigned));
+    // Workgroups' counts added with atomics take 26 to 45 ns a workgroup, one after the other (more the more bins
+    // are counted); written and summed by a second launch, 5 us and 2.7 ps for each counter of each workgroup.
+    // 900 atoms 8x8 (208 workgroups): 800 counters 12.3 us with atomics and 10.3 summed, 12 000 counters 14.0 and
+    // 19.0; 3000 atoms (726) 30.2 and 12.5, 38.2 and 32.0; 96 000 atoms (768) 66.8 and 50.0, 115.4 and 86.9.
+    const long counters = (long)nt * nt * nbins;
+    if ((double)nb * (42e-3 - 2.7e-6 * (double)counters) > 5.0)
+        a.parts = (unsigned *)ctx->rdf_parts.get(ctx, (size_t)counters * kRdfGroups * sizeof(unsigned));
     if (g->m == 4 && g->nn == 4) k_rdf<4, 4><<<nb, 64 * kRdfWaves, lds, st>>>(a);
     else if (g->m == 4 && g->nn == 8) k_rdf<4, 8><<<nb, 64 * kRdfWaves, lds, st>>>(a);
     else if (g->m == 8 && g->nn == 4) k_rdf<8, 4><<<nb, 64 * kRdfWaves, lds, st>>>(a);
