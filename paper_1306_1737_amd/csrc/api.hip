@@ -462,7 +462,7 @@ int nb_pairlist_build(nb_ctx *c, const nb_grid *g, float rlist, float rbb, const
     rc = rc ? rc : ensure(l->ctx, l->part_count, nreg * 4);
     rc = rc ? rc : ensure(l->ctx, l->part_start, nreg * 4);
     rc = rc ? rc : ensure(l->ctx, l->part_istart, nreg * 4);
-    rc = rc ? rc : ensure(l->ctx, l->totals, 32);
+    rc = rc ? rc : ensure(l->ctx, l->totals, 16);
     // entry and item capacities are set by the reserving (synchronous) build
     if (rc == NB_OK) {
         ScopedTimer tm(c, NB_TIMER_PAIRLIST);

@@ -31,7 +31,6 @@ struct SearchArgsT {
     P<const float4> xs;
     P<const int> perm, slot_of;
     P<const float4> bbi_lo, bbi_hi, bbj_lo, bbj_hi, colbb;
-    P<const int> col_start;
     P<const int> zfirst;                 // (x, y) per (column, z bin), see z_index in grid.hip
     P<const int> excl_off, excl_idx;
     float Lx, Ly, Lz, inv_x, inv_y, inv_z;
@@ -60,7 +59,6 @@ __device__ inline SearchArgsG to_global(const SearchArgs &a) {
     g.bbj_lo = (gptr<const float4>)a.bbj_lo;
     g.bbj_hi = (gptr<const float4>)a.bbj_hi;
     g.colbb = (gptr<const float4>)a.colbb;
-    g.col_start = (gptr<const int>)a.col_start;
     g.zfirst = (gptr<const int>)a.zfirst;
     g.excl_off = (gptr<const int>)a.excl_off;
     g.excl_idx = (gptr<const int>)a.excl_idx;
@@ -948,7 +946,7 @@ struct ListJob {
     SearchArgs a;
     FinishArgs f;
 };
-static_assert(sizeof(SearchArgs) == 20 * sizeof(void *) + 16 * sizeof(int) &&
+static_assert(sizeof(SearchArgs) == 19 * sizeof(void *) + 16 * sizeof(int) &&
                   sizeof(FinishArgs) == 11 * sizeof(void *) + 2 * sizeof(long) + 8 * sizeof(int) &&
                   sizeof(ListJob) == sizeof(SearchArgs) + sizeof(FinishArgs),
               "a job table has padding");
@@ -1002,7 +1000,6 @@ static SearchArgs make_search(const nb_list *l, const int *excl_off, const int *
     a.bbj_lo = (const float4 *)(g->nn == g->m ? g->bbi_lo.p : g->bbj_lo.p);
     a.bbj_hi = (const float4 *)(g->nn == g->m ? g->bbi_hi.p : g->bbj_hi.p);
     a.colbb = (const float4 *)g->colbb.p;
-    a.col_start = (const int *)g->col_start.p;
     a.zfirst = (const int *)g->zfirst.p;
     a.excl_off = excl_off;
     a.excl_idx = excl_idx;
@@ -1342,7 +1339,7 @@ int launch_prune(nb_list *in, const nb_list *outer, float r) {
     int rc = ensure(in->ctx, in->part_count, nreg * 4);
     rc = rc ? rc : ensure(in->ctx, in->part_start, nreg * 4);
     rc = rc ? rc : ensure(in->ctx, in->part_istart, nreg * 4);
-    rc = rc ? rc : ensure(in->ctx, in->totals, 32);
+    rc = rc ? rc : ensure(in->ctx, in->totals, 16);
     rc = rc ? rc : ensure(in->ctx, in->entries, (size_t)outer->cap_entries * sizeof(nb_jentry));
     rc = rc ? rc : ensure(in->ctx, in->items, (size_t)outer->cap_items * sizeof(int4));
     const long nsc = (long)kRankSets * rank_stride(njc);
@@ -1355,7 +1352,7 @@ int launch_prune(nb_list *in, const nb_list *outer, float r) {
     if (rc) return rc;
     if (in->jcount.bytes != old_jc || in->resv_nci != outer->resv_nci)
         MXN_HIP(hipMemsetAsync(in->jcount.p, 0, (size_t)nsc * 4, st));
-    if (in->totals.bytes != old_tot) MXN_HIP(hipMemsetAsync(in->totals.p, 0, 32, st));
+    if (in->totals.bytes != old_tot) MXN_HIP(hipMemsetAsync(in->totals.p, 0, 16, st));
     in->grid = g;
     in->grid_generation = outer->grid_generation;
     in->rlist = r;
