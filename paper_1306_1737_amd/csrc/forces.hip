@@ -100,11 +100,14 @@ struct ForceArgs {
 // slot was sorted with (packed image offsets, 10 bits per axis, biased by 512):
 // x - (float)k * L with the product and the difference rounded separately,
 // the definition the list's particle tests are checked against (a contracted
-// multiply-add differs once k * L is inexact, for inputs many boxes away).
+// multiply-add differs once k * L is inexact, for inputs three boxes away and
+// more; __fmul_rn and __fsub_rn are plain operations here, which this file's
+// default contraction joins like any others).
 __device__ inline float4 apply_image(float4 p, int im, float Lx, float Ly, float Lz) {
-    p.x = __fsub_rn(p.x, __fmul_rn((float)((im & 1023) - 512), Lx));
-    p.y = __fsub_rn(p.y, __fmul_rn((float)(((im >> 10) & 1023) - 512), Ly));
-    p.z = __fsub_rn(p.z, __fmul_rn((float)(((im >> 20) & 1023) - 512), Lz));
+#pragma clang fp contract(off)
+    p.x = p.x - (float)((im & 1023) - 512) * Lx;
+    p.y = p.y - (float)(((im >> 10) & 1023) - 512) * Ly;
+    p.z = p.z - (float)(((im >> 20) & 1023) - 512) * Lz;
     return p;
 }
 
@@ -1504,7 +1507,7 @@ void set_ewald_poly(ForceArgs &a, float beta) {
 
 // Systems up to this many slots take no gather launch (2.3 us and the gap behind it): their force kernel reads
 // the particles through the permutation, one more load in the chain of a wavefront that has little to overlap it
-// with anyway.  900 atoms 16.8 -> 15.7 us a call, 12 000 (8x4) 29.1 -> 28.5; at 24 000 (4x8) 40.2 -> 42.0, and at
+// with anyway.  900 atoms 16.8 -> 15.8 us a call, 12 000 (8x4) 29.1 -> 28.5; at 24 000 (4x8) 40.2 -> 42.0, and at
 // 96 000 the extra load costs 13 us.
 constexpr int kOwnSlots = 16384;
 
