@@ -39,8 +39,8 @@ PEAK_FP32 = 157.3e12
 # HBM traffic of one force-kernel launch on this workload: rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE
 # (KiB per dispatch), each scaled by what the same counter reads for a 256 MiB device-to-device copy
 # (FETCH_SIZE x2.0, WRITE_SIZE x1.0).  Valid only for the kernel sources the counters were taken on.
-FORCE_TRAFFIC = {"sources_sha1": "6dbd09e2c8486cb1568466a6c676ea4fcbfc45a1", "fetch_kib": 16286.6,
-                 "write_kib": 106222.0, "fetch_scale": 2.0, "write_scale": 1.0}
+FORCE_TRAFFIC = {"sources_sha1": "c21f2840752cadbb0feeb5d12821299052ef936e", "fetch_kib": 16228.9,
+                 "write_kib": 106148.6, "fetch_scale": 2.0, "write_scale": 1.0}
 FORCE_SOURCES = ("paper_1306_1737_amd/csrc/forces.hip", "paper_1306_1737_amd/csrc/devptr.h",
                  "paper_1306_1737_amd/csrc/ewald_fit.h")
 METRIC = "atom-pair interactions/s (FP32, ≤1e-5 rel force err) + % FP32 VALU peak"

@@ -104,9 +104,18 @@ typedef struct {
  *                               that stream may still use it (stream order)
  * Blocks are requested when a handle grows (the first grid sort, list build
  * or force call of a size, nb_batch_create, nb_mlp_create, ...) and returned
- * when it is freed or grows again; never inside a captured graph.  After
- * nb_set_stream, synchronise the old stream before freeing handles whose
- * blocks came from it. */
+ * when it is freed or grows again; never inside a captured graph.  nb_rdf and
+ * the training calls nb_mlp_train_step and nb_mlp_grad also request scratch,
+ * on the first call that can use it on a stream: a block for each of up to
+ * four streams, held by the context (nb_rdf, at most 48 MB each: 768
+ * histograms) or the model (2.5 MB each); the block that a further stream
+ * takes over, once 64 calls have gone by without it, is returned and requested
+ * anew on that stream.  They need none to succeed: refused it, on a stream
+ * without a block, on the per-thread default stream and while the stream is
+ * being captured they take a slower form (256 samples 144 us instead of 13, a
+ * 96 000-atom histogram 67 us instead of 50; sums in another order, counts the
+ * same).  After nb_set_stream, synchronise the old stream before freeing
+ * handles whose blocks came from it, or destroying it. */
 typedef struct {
     void *(*alloc)(size_t bytes, void *stream, void *user);
     void (*free)(void *ptr, void *stream, void *user);
@@ -278,7 +287,10 @@ enum { NB_RDF_SKIP_EXCLUDED = 1 };
 int nb_rdf(nb_ctx *ctx, const nb_grid *grid, const nb_list *list, const float *xyzq_now, float r_max, int nbins,
            int ntypes, int flags, unsigned long long *hist);
 
-/* Synchronous.  Number of cluster-pair entries and force work items. */
+/* Synchronous.  Number of cluster-pair entries and force work items (one
+ * wavefront's entries in the force kernel: 256/N at most, 128/N or 64/N in
+ * lists so short that they would not fill the GPU otherwise, and chosen by
+ * each synchronous build: forces do not depend on it beyond FP32 rounding). */
 int nb_list_info(nb_list *list, long *n_entries, long *n_items);
 
 /* One cluster pair in canonical form: i-cluster, image shift index
@@ -408,6 +420,13 @@ int nb_set_search_parts(nb_ctx *ctx, int parts);
  * graph must then be captured again (nb_batch_replay returns NB_ERR_STATE).
  * The graph keeps the params' c6c12 pointer and the output pointers passed
  * to nb_batch_capture.  Supported flags: NB_ENERGY, NB_VIRIAL, NB_ACCUMULATE.
+ * nb_batch_create cuts lists that hold short work items into full ones (the
+ * replicas fill the GPU together), which nb_list_info then counts: it waits
+ * for the device before and for the context's stream after.  Such a list keeps
+ * full items at its synchronous builds until its batches are freed; a batch
+ * and its lists may be freed in either order, and a batch that could not be
+ * created leaves the lists as they were.  A replica whose grid is sorted in
+ * another cluster shape is refused with NB_ERR_STATE.
  * Every Coulomb variant of nb_params (Eq. 2: analytic Ewald, reaction field,
  * tabulated Ewald); the tabulated variant's table is built in the context on
  * first use, and before a capture begins, so captured launches only read it.
@@ -575,7 +594,9 @@ int nb_mlp_create(nb_ctx *ctx, const float *params_host, const double lo[8], con
 void nb_mlp_free(nb_mlp *mlp);
 /* Synchronous copy of the current parameters to HOST params[NB_MLP_PARAMS]. */
 int nb_mlp_get_params(nb_mlp *mlp, float *params);
-/* One Adam step on a minibatch (one workgroup); loss: DEVICE float or NULL. */
+/* One Adam step on a minibatch; loss: DEVICE float or NULL.  Up to eight
+ * samples, and without scratch (see nb_allocator), on one workgroup, more on up
+ * to 128, whose sums are added in a fixed order. */
 int nb_mlp_train_step(nb_ctx *ctx, nb_mlp *mlp, const float *X, const float *y, int batch, float lr, float *loss);
 /* Gradient of the batch loss (DEVICE float[NB_MLP_PARAMS]) without updating the model. */
 int nb_mlp_grad(nb_ctx *ctx, nb_mlp *mlp, const float *X, const float *y, int batch, float *grad, float *loss);

@@ -3,8 +3,8 @@
 // GPU as the paper planned.  One wavefront per i-cluster: for each kept image
 // shift it walks the candidate grid columns in increasing column order and
 // tests that column's j-clusters 64 at a time (one per lane) against the
-// bounding-box criterion; a lane whose candidate lies outside the rBB
-// shortcut checks the candidate's particle pairs itself.  A count pass, a
+// bounding-box criterion; the particle pairs of the candidates that lie outside
+// the rBB shortcut are checked by the whole wavefront.  A count pass, a
 // deterministic scan and a fill pass give a list whose order depends only on
 // the input.
 //
@@ -374,9 +374,10 @@ __device__ inline void search_body(const A &a, int blk) {
 }
 
 template <int M, int N, bool FILL>
-// Six wavefronts per SIMD (at most 80 VGPRs): 50.8 us on the 96 000-atom 8x8 list against 53.3 at seven, which
-// spill (3 million atoms: 1.01 against 1.11 ms).  Of the 50.8 us the rank atomics, about 58 G/s over the whole chip,
-// are 17 (without them 34); taking them in one go at the wavefront's end measured 49, and 2 % slower at 3 million.
+// Six wavefronts per SIMD (at most 80 VGPRs): 45.7 us on the 96 000-atom 8x8 list.  With one set of rank counters it
+// took 50.8, against 53.3 at seven wavefronts, which spill (3 million atoms: 1.01 against 1.11 ms); of the 50.8 the
+// rank atomics, about 58 G/s over the whole chip, were 17 (without them 34), and taken in one go at the wavefront's
+// end it was 49, and 2 % slower at 3 million.
 __attribute__((amdgpu_waves_per_eu(6)))
 __global__ __launch_bounds__(256) void k_search(SearchArgs a) {
     search_body<M, N, FILL>(a, blockIdx.x);
@@ -696,7 +697,7 @@ __global__ void k_items(int nparts_total, int parts, int per_item, const int *pa
 // Second stage of a two-stage list (Sec. 2.3: the list built from bounding
 // boxes, then cluster pairs whose particles are all beyond a radius removed
 // by a particle-distance test on the GPU).  One wavefront per region of the
-// outer list, one lane per entry: an entry is kept iff a real particle of
+// outer list: an entry is kept iff a real particle of
 // the i-cluster, moved by the entry's image shift, and a real particle of
 // the j-cluster are closer than r, formed with the search's own separately
 // rounded FP32 operations, at the gathered positions of the call.  Kept
@@ -720,9 +721,9 @@ struct PruneArgs {
 
 // Lane = (entry, j-particle), 64/N entries a step: an entry's particles are one coalesced 16 N-byte run (one lane per
 // entry read N scattered particles and N permutation words).  The i-particles
-// moved by an image shift are formed once per run of equal shifts.  Bound by
-// VALU issue (125 instructions a step), 56 us for 1.6 M entries (66 us with one
-// lane per entry), of which the rank atomics are 11.
+// moved by an image shift are formed once per run of equal shifts.  54 us for
+// 1.6 M entries (66 us with one lane per entry): the issue of 117 vector
+// instructions a step, 32 to 40 us, and the rank atomics, 11.
 template <int M, int N>
 __global__ __launch_bounds__(256) void k_prune(PruneArgs a) {
     constexpr int G = 64 / N;

@@ -19,10 +19,11 @@
 // separately rounded operations; this file is compiled with
 // -ffp-contract=off).
 //
-// Bound: VALU issue (26 instructions per listed pair, 64 with an IEEE square
-// root and both edges read for every pair), 57 us of the 96 000-atom frame
-// (113 us before), and the workgroups' histograms: flushed with global atomics
-// by 768 workgroups they took 25 us, written to scratch and summed by a second
+// Bound: 26 vector instructions per listed pair (64 with an IEEE square root
+// and both edges read for every pair), whose issue takes 33 to 49 of the
+// 96 000-atom frame's 57 us (113 us before), beside the LDS atomics, one a
+// counted pair; and the workgroups' histograms: flushed with global atomics by
+// 768 workgroups they took 25 us, written to scratch and summed by a second
 // launch 5 us.
 #include <cmath>
 #include <type_traits>
