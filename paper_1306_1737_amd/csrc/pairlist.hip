@@ -460,6 +460,11 @@ __global__ __launch_bounds__(1024) void k_max_count(const int *in, int n, int pe
     }
 }
 
+// Cleared counters (no memset: these launches may be captured, and memset nodes have given wrong results on replays).
+__global__ void k_clear(int n, int *p) {
+    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) p[k] = 0;
+}
+
 // Uniform regions (region g starts at g * size, g = 0 .. n), cleared j-cluster counters and overflow mark.
 __global__ void k_reserve(int n, int size, int *start, int njc, int *jcount, int *totals) {
     const int g = blockIdx.x * blockDim.x + threadIdx.x;
@@ -989,6 +994,10 @@ void run(nb_list *l, SearchArgs &a, bool fill, int nblocks, hipStream_t st) {
 
 namespace mxn {
 
+static void clear_ints(void *p, long n, hipStream_t st) {
+    k_clear<<<(int)std::min(1024L, (n + 255) / 256), 256, 0, st>>>((int)n, (int *)p);
+}
+
 static SearchArgs make_search(const nb_list *l, const int *excl_off, const int *excl_idx) {
     const nb_grid *g = l->grid;
     SearchArgs a{};
@@ -1266,7 +1275,7 @@ int launch_sci_view(const nb_list *l, int S, int per_item) {
     const int ngroups = (l->resv_nci + S - 1) / S;
     const long njc = g->slots_cap / g->nn;
     const long cap_items = l->cap_entries / per_item + ngroups + 256;
-    void *old_jc = l->sci_jcount.p, *old_tot = l->sci_totals.p;
+    const size_t old_jc = l->sci_jcount.bytes, old_tot = l->sci_totals.bytes;   // larger: new memory, wherever it lies
     int rc = ensure(l->ctx, l->sci_ent, (size_t)l->cap_entries * sizeof(int4));
     rc = rc ? rc : ensure(l->ctx, l->sci_mask, (size_t)l->cap_entries * S * sizeof(uint2));
     rc = rc ? rc : ensure(l->ctx, l->sci_count, (size_t)(ngroups + 1) * 4);
@@ -1278,11 +1287,11 @@ int launch_sci_view(const nb_list *l, int S, int per_item) {
     rc = rc ? rc : ensure(l->ctx, l->sci_totals, 16);
     rc = rc ? rc : ensure(l->ctx, l->sci_fi, (size_t)cap_items * S * 8 * sizeof(float4));
     if (rc) return rc;
-    if (l->sci_jcount.p != old_jc || l->sci_njc != njc) {   // counters start cleared; the scan clears them after use
-        MXN_HIP(hipMemsetAsync(l->sci_jcount.p, 0, (size_t)(njc + 1) * 4, st));
+    if (l->sci_jcount.bytes != old_jc || l->sci_njc != njc) {   // counters start cleared; the scan clears them after use
+        clear_ints(l->sci_jcount.p, njc + 1, st);
         l->sci_njc = njc;
     }
-    if (l->sci_totals.p != old_tot) MXN_HIP(hipMemsetAsync(l->sci_totals.p, 0, 16, st));
+    if (l->sci_totals.bytes != old_tot) clear_ints(l->sci_totals.p, 4, st);
     SciArgs a{};
     a.nslots = (const int *)g->nslots.p;
     a.totals = (const int *)l->totals.p;
@@ -1352,8 +1361,8 @@ int launch_prune(nb_list *in, const nb_list *outer, float r) {
     rc = rc ? rc : ensure(in->ctx, in->fi, (size_t)outer->cap_items * g->m * 16);
     if (rc) return rc;
     if (in->jcount.bytes != old_jc || in->resv_nci != outer->resv_nci)
-        MXN_HIP(hipMemsetAsync(in->jcount.p, 0, (size_t)nsc * 4, st));
-    if (in->totals.bytes != old_tot) MXN_HIP(hipMemsetAsync(in->totals.p, 0, 16, st));
+        clear_ints(in->jcount.p, nsc, st);
+    if (in->totals.bytes != old_tot) clear_ints(in->totals.p, 4, st);
     in->grid = g;
     in->grid_generation = outer->grid_generation;
     in->rlist = r;
